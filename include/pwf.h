@@ -440,11 +440,11 @@ size_t pwf_shell_correlation_workspace_size(int32_t n, int32_t dims);
  * arrays g1, g2 of n^dims elements (e.g. two pwf_fbp volumes of n slices):
  *   fsc[kappa] = Re sum G1* G2 / sqrt(sum |G1|^2 sum |G2|^2) over the shell
  *   kappa = round(|k|) of signed index frequencies, kappa = 0 .. n/2.
- * The resolution criterion of the paper is fsc = 1/4 (Eqs. 17-18).  The two
- * real fields, each scaled to unit RMS (which leaves fsc unchanged), are
- * transformed together as one complex field (FP32): a shell where one input's
- * amplitude is a fraction r of the other's carries an absolute error of about
- * 1e-7 / r.  Shell sums in FP64 in a fixed order (bit-reproducible from call
+ * The resolution criterion of the paper is fsc = 1/4 (Eqs. 17-18).  Each real
+ * field has FP32 transforms of its own (half spectra), so the rounding of one
+ * does not reach the other whatever their sizes; an input whose spectrum would
+ * leave the FP32 range is transformed again at unit RMS (positive scaling does
+ * not change fsc).  Shell sums in FP64 in a fixed order (bit-reproducible from call
  * to call).  fsc_out: HOST float64 [n/2 + 1]; the call synchronises on
  * `stream`. */
 pwf_status pwf_shell_correlation(const void* g1, const void* g2, int32_t n, int32_t dims, int32_t part,

@@ -2017,7 +2017,7 @@ pwf_status pwf_background_quadratic(void* vol, int32_t n_slices, int32_t n, doub
 // ------------------------------------------------------------ shell correlation
 
 namespace {
-// workspace: the packed field and its DFT (one complex n^dims array), the
+// workspace: the half spectra of both fields (one complex n^dims array), the
 // workgroups' shell partials, the shell sums
 bool fsc_layout(int n, int dims, size_t* part_off, size_t* out_off, size_t* total) {
   if ((dims != 2 && dims != 3) || size_index(n) < 0) return false;
@@ -2053,21 +2053,39 @@ pwf_status pwf_shell_correlation(const void* g1, const void* g2, int32_t n, int3
   float2* X = (float2*)ws;
   const float2* twr = ctx->tw[size_index(n)];
   const float2* twc = ctx->twc[size_index(n)];
-  // both parts in one complex field, then its n^dims DFT as 1-D transforms
-  // along x, y (per z plane) and z; the shell sums separate the two spectra
-  // (the unit-RMS scales live in the shell-sum area until the sums overwrite it)
-  PWF_HIP(pwf::launch_fsc_pack((const float2*)g1, (const float2*)g2, part, X, m, (double*)(ws + part_off),
-                               (float*)(ws + out_off), st));
-  PWF_HIP(pwf::launch_plain_rows(n, -1, X, X, (int)(m / n), twr, st));
-  const int planes = dims == 3 ? n : 1;
-  PWF_HIP(pwf::launch_plain_cols(n, -1, X, n, twc, st, planes, (size_t)n * n));
-  if (dims == 3) PWF_HIP(pwf::launch_plain_cols(n, -1, X, n * n, twc, st));
   double* out = (double*)(ws + out_off);
-  PWF_HIP(pwf::launch_fsc_shells(X, n, dims, (double*)(ws + part_off), out, st));
   const int nsh = n / 2 + 1;
   std::vector<double> h(3 * (size_t)nsh);
-  PWF_HIP(hipMemcpyAsync(h.data(), out, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
-  PWF_HIP(hipStreamSynchronize(st));
+  // Powers of two on the inputs (exact, and the correlation does not change
+  // under positive scaling): 1 unless an input is so small or large that its
+  // FP32 spectrum would leave the normal range.  The shell powers tell, by
+  // Parseval: sum |2 G|^2 <= 4 m^2 RMS^2.  Such an input is transformed again
+  // at unit RMS; one whose sums are not finite is first scaled down (an
+  // overflow then shows its size, a NaN or Inf input stays what it is).
+  int e[2] = {0, 0};
+  for (int pass = 0; pass < 3; ++pass) {
+    PWF_HIP(pwf::launch_fsc((const float2*)g1, (const float2*)g2, n, dims, part, std::ldexp(1.f, e[0]),
+                            std::ldexp(1.f, e[1]), X, twr, twc, ctx->twn[size_index(n)], (double*)(ws + part_off), out,
+                            st));
+    PWF_HIP(hipMemcpyAsync(h.data(), out, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
+    PWF_HIP(hipStreamSynchronize(st));
+    bool again = false;
+    for (int f = 0; f < 2; ++f) {
+      double power = 0.0;
+      for (int s = 0; s < nsh; ++s) power += h[(f + 1) * (size_t)nsh + s];
+      int shift = 0;
+      if (!std::isfinite(power)) {
+        shift = e[f] == 0 ? -100 : 0;
+      } else {
+        const double rms = std::sqrt(power) / (2.0 * (double)m);
+        if (rms < 0x1p-60 || rms > 0x1p50) shift = rms > 0.0 ? -std::ilogb(rms) : (e[f] == 0 ? 100 : 0);
+      }
+      shift = std::max(-126, std::min(126, e[f] + shift)) - e[f];   // (a normal FP32 factor)
+      e[f] += shift;
+      again = again || shift != 0;
+    }
+    if (!again) break;
+  }
   // Eq. 16: shell cross-correlation over the geometric mean of the shell powers
   for (int s = 0; s < nsh; ++s) fsc_out[s] = h[s] / std::sqrt(h[nsh + s] * h[2 * nsh + s]);
   return PWF_OK;

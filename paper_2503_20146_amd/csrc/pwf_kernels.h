@@ -117,13 +117,15 @@ hipError_t launch_fbp_pad(const float2* const* psi, int n_proj, int nx, int ny, 
 hipError_t launch_fbp_ramp(float2* a, const float* h, int n_pad, size_t rows, hipStream_t st);
 hipError_t launch_fbp_backproject(const float2* q, int n_proj, int nx, int ny, int n_pad, const float2* cs, int n_out,
                                   float scale, float2* vol, hipStream_t st);
-// Fourier shell correlation (pwf_tomo.hip): out[s], out[nsh + s], out[2 nsh + s]
-// = shell sums of Re(G1* G2), |G1|^2, |G2|^2, nsh = n/2 + 1.
+// Fourier shell correlation (pwf_fsc.hip) of g1 times s1 and g2 times s2: out[s],
+// out[nsh + s], out[2 nsh + s] = shell sums of Re(G1* G2), |G1|^2, |G2|^2 (times a
+// common factor), nsh = n/2 + 1.  X: n^dims elements of scratch; partial:
+// fsc_blocks() rows of 3 nsh doubles; tw_row, tw_col: the side's row- and
+// column-plan twiddles; twn: w_n^m.
 int fsc_blocks();
-// (partial: 2 fsc_blocks() doubles of scratch; scale: 2 floats of device memory)
-hipError_t launch_fsc_pack(const float2* g1, const float2* g2, int part, float2* dst, size_t m, double* partial,
-                           float* scale, hipStream_t st);
-hipError_t launch_fsc_shells(const float2* spec, int n, int dims, double* partial, double* out, hipStream_t st);
+hipError_t launch_fsc(const float2* g1, const float2* g2, int n, int dims, int part, float s1, float s2, float2* X,
+                      const float2* tw_row, const float2* tw_col, const float2* twn, double* partial, double* out,
+                      hipStream_t st);
 // Quadratic background removal (pwf_tomo.hip): n a multiple of 16; slices are
 // split into bands of bg_rows_per_band(n) rows (n a multiple of that).
 // partial: n_slices * (n / rows) * 12 doubles; minv: the inverse 6 x 6 normal

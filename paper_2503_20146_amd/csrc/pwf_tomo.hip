@@ -142,241 +142,6 @@ hipError_t launch_fbp_backproject(const float2* q, int n_proj, int nx, int ny, i
 
 namespace pwf {
 
-// Fourier shell correlation (Methods, Eq. 16) of the chosen parts (0 real,
-// 1 imaginary) of two complex volumes.  Both real fields go into one complex
-// field c = a + i b, whose single DFT C holds both spectra:
-//   A(k) = (C(k) + conj C(-k)) / 2,   B(k) = (C(k) - conj C(-k)) / (2 i),
-// one transform instead of two.  The rounding of each spectrum is then
-// relative to the larger of the two at that frequency, so a and b are first
-// scaled to unit RMS: the correlation does not change under positive scaling
-// of either input, and inputs of any relative size keep FP32 accuracy.
-constexpr int kFscThreads = 256;
-
-// FP64 sums of a^2 and b^2 per workgroup, in a fixed order.
-__global__ void __launch_bounds__(kFscThreads) fsc_norm_kernel(const float2* __restrict__ g1,
-                                                               const float2* __restrict__ g2, int part, size_t m,
-                                                               double* __restrict__ partial) {
-  double sa = 0.0, sb = 0.0;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < m; i += (size_t)gridDim.x * blockDim.x) {
-    const float2 u = g1[i], v = g2[i];
-    const double a = part ? u.y : u.x, b = part ? v.y : v.x;
-    sa = fma(a, a, sa);
-    sb = fma(b, b, sb);
-  }
-  __shared__ double red[kFscThreads / 64][2];
-  for (int off = 32; off > 0; off >>= 1) {
-    sa += __shfl_xor(sa, off, 64);
-    sb += __shfl_xor(sb, off, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[threadIdx.x >> 6][0] = sa;
-    red[threadIdx.x >> 6][1] = sb;
-  }
-  __syncthreads();
-  if (threadIdx.x < 2) {
-    double t = 0.0;
-    for (int w = 0; w < kFscThreads / 64; ++w) t += red[w][threadIdx.x];
-    partial[2 * (size_t)blockIdx.x + threadIdx.x] = t;
-  }
-}
-
-// scale[p] = 1 / RMS of field p (1 for a field of zeros), the partials summed in order
-__global__ void fsc_scale_kernel(const double* __restrict__ partial, int blocks, size_t m, float* __restrict__ scale) {
-  if (threadIdx.x < 2) {
-    double t = 0.0;
-    for (int b = 0; b < blocks; ++b) t += partial[2 * (size_t)b + threadIdx.x];
-    scale[threadIdx.x] = t > 0.0 ? (float)(1.0 / sqrt(t / (double)m)) : 1.f;
-  }
-}
-
-__global__ void fsc_pack_kernel(const float2* __restrict__ g1, const float2* __restrict__ g2, int part,
-                                const float* __restrict__ scale, float2* __restrict__ dst, size_t m) {
-  const float sa = scale[0], sb = scale[1];
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < m; i += (size_t)gridDim.x * blockDim.x) {
-    const float2 a = g1[i], b = g2[i];
-    dst[i] = part ? make_float2(a.y * sa, b.y * sb) : make_float2(a.x * sa, b.x * sb);
-  }
-}
-
-// Shell sums of Re(G1* G2), |G1|^2, |G2|^2 over kappa = round(|k|) (signed
-// index frequencies of an n^dims grid), kappa <= n/2, in a fixed order (the
-// result is bit-reproducible).  Every wave owns a private histogram of the
-// three sums in LDS and walks its share of the grid in chunks of 64 K
-// consecutive elements, K per lane.  A chunk lies in one half of one x row
-// (64 K divides n/2), where kappa is monotone in kx, so equal kappa form runs
-// of consecutive elements:
-//  * each lane sums its own K elements run by run; a run that starts and ends
-//    inside the lane is complete and goes to the histogram at once (no other
-//    lane holds that kappa);
-//  * the lane's first and last runs may continue runs of its neighbours.  A
-//    lane whose K elements are one run passes the sum arriving from the left
-//    on (when kappa matches) plus its own; any other lane starts afresh with
-//    its last run.  That is the map x -> A x + B per lane (A = 1 for a
-//    continuing single-run lane, else 0), composed over the wave by an
-//    inclusive scan in a fixed butterfly order;
-//  * a lane with several runs adds the sum arriving from the left to its first
-//    run and writes that; a lane whose last run the next lane does not
-//    continue writes its scan value.
-// The kappa written by the lanes of one store are distinct, so no two lanes
-// of a wave touch one entry at once, and the stores follow program order.
-// The workgroup then adds its waves' histograms in wave order and writes one
-// row of partials.  Four waves per workgroup up to n = 1024 and two at 2048
-// keep the histograms at 49 KB of LDS.
-
-template <int K>
-__global__ void __launch_bounds__(kFscThreads) fsc_shell_kernel(const float2* __restrict__ spec, int n, int dims,
-                                                                double* __restrict__ partial) {
-  extern __shared__ double sh[];
-  const int nsh = n / 2 + 1;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-  for (int i = threadIdx.x; i < waves * 3 * nsh; i += blockDim.x) sh[i] = 0.0;
-  __syncthreads();
-  double* h = sh + wave * 3 * nsh;
-  const size_t m = dims == 3 ? (size_t)n * n * n : (size_t)n * n;
-  const size_t chunks = m / (64 * K);
-  const size_t stride = (size_t)gridDim.x * waves;
-  const int lg = 31 - __clz(n);  // n is a power of two
-  auto put = [&](int k, double x0, double x1, double x2) {
-    if (k < nsh) {
-      h[k] += x0;
-      h[nsh + k] += x1;
-      h[2 * nsh + k] += x2;
-    }
-  };
-  for (size_t c = (size_t)blockIdx.x * waves + wave; c < chunks; c += stride) {
-    const size_t e0 = c * (64 * K) + (size_t)lane * K;  // this lane's first element
-    const size_t row = e0 >> lg;
-    const int kx0 = (int)(e0 & (size_t)(n - 1));
-    const int ky = (int)(row & (size_t)(n - 1));
-    const int kz = (int)(row >> lg);  // 0 in 2-D
-    const float fy = (float)(ky < n / 2 ? ky : ky - n);
-    const float fz = (float)(kz < n / 2 ? kz : kz - n);
-    const float r2 = fy * fy + fz * fz;
-    int sk[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const int kx = kx0 + j;
-      const float fx = (float)(kx < n / 2 ? kx : kx - n);
-      const int k = (int)rintf(sqrtf(fx * fx + r2));
-      sk[j] = k < nsh ? k : nsh;  // nsh: outside the last shell
-    }
-    // kappa is monotone over the lane's elements: one inside means an end is.
-    // C(k) and C(-k) (same shell): -k is (n - kx, n - ky, n - kz) mod n.
-    float2 ck[K], cm[K];
-    const bool any_in = sk[0] < nsh || sk[K - 1] < nsh;
-    const size_t mrow = (((size_t)((n - kz) & (n - 1)) * n + (size_t)((n - ky) & (n - 1)))) * n;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      ck[j] = any_in ? spec[e0 + j] : make_float2(0.f, 0.f);
-      cm[j] = any_in ? spec[mrow + ((n - kx0 - j) & (n - 1))] : make_float2(0.f, 0.f);
-    }
-    // runs inside the lane: f = first run, q = current run
-    double f0 = 0.0, f1 = 0.0, f2 = 0.0, q0 = 0.0, q1 = 0.0, q2 = 0.0;
-    int sf = sk[0], sq = sk[0];
-    bool multi = false;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      // A = ((Cr + Cmr) + i (Ci - Cmi)) / 2,  B = ((Ci + Cmi) + i (Cmr - Cr)) / 2
-      const double ax = 0.5 * ((double)ck[j].x + cm[j].x), ay = 0.5 * ((double)ck[j].y - cm[j].y);
-      const double bx = 0.5 * ((double)ck[j].y + cm[j].y), by = 0.5 * ((double)cm[j].x - ck[j].x);
-      double v0 = ax * bx + ay * by;
-      double v1 = ax * ax + ay * ay;
-      double v2 = bx * bx + by * by;
-      if (sk[j] == nsh) v0 = v1 = v2 = 0.0;
-      if (j == 0) {
-        f0 = v0;
-        f1 = v1;
-        f2 = v2;
-      } else if (sk[j] == sq) {
-        if (multi) {
-          q0 += v0;
-          q1 += v1;
-          q2 += v2;
-        } else {
-          f0 += v0;
-          f1 += v1;
-          f2 += v2;
-        }
-      } else {
-        if (multi) put(sq, q0, q1, q2);  // a run inside the lane is complete
-        multi = true;
-        sq = sk[j];
-        q0 = v0;
-        q1 = v1;
-        q2 = v2;
-      }
-    }
-    const int sl = multi ? sq : sf;  // kappa of the lane's last run
-    const int sl_prev = __shfl_up(sl, 1, 64);
-    const bool join = lane > 0 && sl_prev == sf;
-    int A = !multi && join ? 1 : 0;
-    double B0 = multi ? q0 : f0, B1 = multi ? q1 : f1, B2 = multi ? q2 : f2;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int Ap = __shfl_up(A, d, 64);
-      const double P0 = __shfl_up(B0, d, 64);
-      const double P1 = __shfl_up(B1, d, 64);
-      const double P2 = __shfl_up(B2, d, 64);
-      if (lane >= d) {
-        if (A) {
-          B0 += P0;
-          B1 += P1;
-          B2 += P2;
-        }
-        A &= Ap;
-      }
-    }
-    // B is now the sum of this lane's last run and the run it continues
-    const double in0 = __shfl_up(B0, 1, 64), in1 = __shfl_up(B1, 1, 64), in2 = __shfl_up(B2, 1, 64);
-    if (multi) put(sf, join ? f0 + in0 : f0, join ? f1 + in1 : f1, join ? f2 + in2 : f2);
-    const int sf_next = __shfl_down(sf, 1, 64);
-    if (!(lane < 63 && sf_next == sl)) put(sl, B0, B1, B2);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 3 * nsh; i += blockDim.x) {
-    double t = sh[i];
-    for (int w = 1; w < waves; ++w) t += sh[w * 3 * nsh + i];
-    partial[(size_t)blockIdx.x * 3 * nsh + i] = t;
-  }
-}
-
-__global__ void fsc_final_kernel(const double* __restrict__ partial, int blocks, int len, double* __restrict__ out) {
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < len; j += gridDim.x * blockDim.x) {
-    double t = 0.0;
-    for (int b = 0; b < blocks; ++b) t += partial[(size_t)b * len + j];
-    out[j] = t;
-  }
-}
-
-// three 49 KB workgroups per CU: one round over the 256 CUs
-int fsc_blocks() { return 768; }
-
-hipError_t launch_fsc_pack(const float2* g1, const float2* g2, int part, float2* dst, size_t m, double* partial,
-                           float* scale, hipStream_t st) {
-  hipLaunchKernelGGL(fsc_norm_kernel, dim3(fsc_blocks()), dim3(kFscThreads), 0, st, g1, g2, part, m, partial);
-  hipLaunchKernelGGL(fsc_scale_kernel, dim3(1), dim3(64), 0, st, partial, fsc_blocks(), m, scale);
-  hipLaunchKernelGGL(fsc_pack_kernel, dim3(4096), dim3(256), 0, st, g1, g2, part, scale, dst, m);
-  return hipGetLastError();
-}
-
-hipError_t launch_fsc_shells(const float2* spec, int n, int dims, double* partial, double* out, hipStream_t st) {
-  const int nsh = n / 2 + 1;
-  const int threads = n > 1024 ? kFscThreads / 2 : kFscThreads;
-  const size_t lds = sizeof(double) * (threads / 64) * 3 * nsh;
-  // four elements per lane where 256 divides n/2, else one (64 divides n/2 from n = 128)
-  if (n >= 512)
-    hipLaunchKernelGGL(fsc_shell_kernel<4>, dim3(fsc_blocks()), dim3(threads), lds, st, spec, n, dims, partial);
-  else
-    hipLaunchKernelGGL(fsc_shell_kernel<1>, dim3(fsc_blocks()), dim3(threads), lds, st, spec, n, dims, partial);
-  hipLaunchKernelGGL(fsc_final_kernel, dim3((3 * nsh + 255) / 256), dim3(256), 0, st, partial, fsc_blocks(),
-                     3 * nsh, out);
-  return hipGetLastError();
-}
-
-}  // namespace pwf
-
-namespace pwf {
-
 // Quadratic background removal after tomography (Methods, "Reconstruction
 // procedure"): per slice, the least-squares quadratic in x, z (voxel-centre
 // coordinates over n/2) fitted separately to the real and imaginary parts of
