@@ -1819,6 +1819,9 @@ int fbp_pad_length(int nx) {
   return p;
 }
 
+// a filtered row: nx samples between two zeros, rows on 128-byte lines
+int fbp_pitch(int nx) { return (nx + 2 + 15) / 16 * 16; }
+
 struct FbpLayout {
   size_t q = 0, ramp = 0, cs = 0, ptrs = 0, total = 0;
 };
@@ -1829,7 +1832,7 @@ bool fbp_layout(int n_proj, int nx, int ny, FbpLayout* L) {
   if (size_index(n_pad) < 0) return false;
   size_t off = 0;
   L->q = off;
-  off += align_up(sizeof(float2) * (size_t)n_proj * ny * n_pad);
+  off += align_up(sizeof(float2) * (size_t)n_proj * ny * fbp_pitch(nx));
   L->ramp = off;
   off += align_up(sizeof(float) * n_pad);
   L->cs = off;
@@ -1884,19 +1887,21 @@ pwf_status pwf_fbp(const void* const* psi, int32_t n_proj, int32_t nx, int32_t n
     }
     H = ramp_cached;
   }
-  std::vector<float2> cs(n_proj);
-  for (int j = 0; j < n_proj; ++j) cs[j] = make_float2((float)std::cos(angles_rad[j]), (float)std::sin(angles_rad[j]));
-  PWF_TRY(upload(*ctx, H.data(), sizeof(float) * n_pad, ws + L.ramp, st));
-  PWF_TRY(upload(*ctx, cs.data(), sizeof(float2) * n_proj, ws + L.cs, st));
-  PWF_TRY(upload(*ctx, psi, sizeof(void*) * n_proj, ws + L.ptrs, st));
+  // ramp, (cos, sin) and the row pointers: one upload
+  std::vector<char> host(L.total - L.ramp);
+  std::memcpy(host.data(), H.data(), sizeof(float) * n_pad);
+  for (int j = 0; j < n_proj; ++j) {
+    const float2 cs = make_float2((float)std::cos(angles_rad[j]), (float)std::sin(angles_rad[j]));
+    std::memcpy(host.data() + (L.cs - L.ramp) + sizeof(float2) * j, &cs, sizeof(cs));
+  }
+  std::memcpy(host.data() + (L.ptrs - L.ramp), psi, sizeof(void*) * n_proj);
+  PWF_TRY(upload(*ctx, host.data(), host.size(), ws + L.ramp, st));
   float2* q = (float2*)(ws + L.q);
-  const size_t rows = (size_t)n_proj * ny;
-  const float2* tw = ctx->tw[size_index(n_pad)];
-  PWF_HIP(pwf::launch_fbp_pad((const float2* const*)(ws + L.ptrs), n_proj, nx, ny, n_pad, q, st));
-  PWF_HIP(pwf::launch_plain_rows(n_pad, -1, q, q, (int)rows, tw, st));
-  PWF_HIP(pwf::launch_fbp_ramp(q, (const float*)(ws + L.ramp), n_pad, rows, st));
-  PWF_HIP(pwf::launch_plain_rows(n_pad, 1, q, q, (int)rows, tw, st));
-  PWF_HIP(pwf::launch_fbp_backproject(q, n_proj, nx, ny, n_pad, (const float2*)(ws + L.cs), n_out,
+  const int pitch = fbp_pitch(nx);
+  PWF_HIP(pwf::launch_fbp_filter((const float2* const*)(ws + L.ptrs), n_proj, nx, ny, n_pad, pitch,
+                                 (const float*)(ws + L.ramp), q, ctx->tw[size_index(n_pad)],
+                                 ctx->twn[size_index(n_pad)], st));
+  PWF_HIP(pwf::launch_fbp_backproject(q, n_proj, nx, ny, pitch, (const float2*)(ws + L.cs), n_out,
                                       (float)(scale * M_PI / n_proj), (float2*)vol_out, st));
   return PWF_OK;
 }

@@ -112,10 +112,12 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 // loss_dst[0] = inv_m * sum of the instance's loss partials, per instance (one workgroup each)
 hipError_t launch_loss_final(const Inst* insts, int n, int32_t* status, hipStream_t st);
 // Filtered back-projection (pwf_tomo.hip)
-hipError_t launch_fbp_pad(const float2* const* psi, int n_proj, int nx, int ny, int n_pad, float2* dst,
-                          hipStream_t st);
-hipError_t launch_fbp_ramp(float2* a, const float* h, int n_pad, size_t rows, hipStream_t st);
-hipError_t launch_fbp_backproject(const float2* q, int n_proj, int nx, int ny, int n_pad, const float2* cs, int n_out,
+// Rows psi[j][y] ramp-filtered over n_pad points into dst, `pitch` >= nx + 2 elements a
+// row: sample i at i + 1, zeros at 0 and nx + 1.
+// ramp: n_pad real responses over n_pad; tw_row, twn: row-plan twiddles and w^m of n_pad.
+hipError_t launch_fbp_filter(const float2* const* psi, int n_proj, int nx, int ny, int n_pad, int pitch,
+                             const float* ramp, float2* dst, const float2* tw_row, const float2* twn, hipStream_t st);
+hipError_t launch_fbp_backproject(const float2* q, int n_proj, int nx, int ny, int pitch, const float2* cs, int n_out,
                                   float scale, float2* vol, hipStream_t st);
 // Fourier shell correlation (pwf_fsc.hip) of g1 times s1 and g2 times s2: out[s],
 // out[nsh + s], out[2 nsh + s] = shell sums of Re(G1* G2), |G1|^2, |G2|^2 (times a
