@@ -1772,39 +1772,25 @@ pwf_status pwf_diffuser_from_reference(const pwf_problem* problem, const float* 
   PWF_TRY(context_for_current(&ctx));
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  const pwf_problem& p = *problem;
-  const int nx = p.geom.nx, ny = p.geom.ny;
-  const size_t m = (size_t)nx * ny;
-  Inst I = base_inst(p);
+  Inst I = base_inst(*problem);
   attach_tables(I, ws, L, 0);
+  I.W = (float2*)(ws + L.W[0]);
   I.y = ref;
+  I.out = (float2*)t_out;
   I.wiener_eps = (float)eps;
   Inst* dI = (Inst*)(ws + L.desc);
   PWF_TRY(upload(*ctx, &I, sizeof(Inst), dI, st));
   PWF_HIP(pwf::launch_build_tables(dI, 1, st));
-  float2* X = (float2*)(ws + L.W[0]);
-  float2* t = (float2*)t_out;
-  double* part = (double*)(ws + L.part[0]);
-  const float2* twx = ctx->tw[size_index(nx)];
-  const float2* twy = ctx->twc[size_index(ny)];
-  auto filter = [&](const float2* src, float2* dst, int window) -> pwf_status {
-    PWF_HIP(pwf::launch_plain_rows(nx, -1, src, dst, ny, twx, st));
-    PWF_HIP(pwf::launch_plain_cols(ny, -1, dst, nx, twy, st));
-    PWF_HIP(pwf::launch_plain_window(dst, dI, window, m, st));
-    PWF_HIP(pwf::launch_plain_cols(ny, 1, dst, nx, twy, st));
-    PWF_HIP(pwf::launch_plain_rows(nx, 1, dst, dst, ny, twx, st));
-    return PWF_OK;
-  };
-  auto ew = [&](int op, const float2* a, float2* out) -> pwf_status {
-    PWF_HIP(pwf::launch_plain_elementwise(op, m, a, nullptr, nullptr, out, dI, ctx->beta, 0, part, st));
-    return PWF_OK;
-  };
   // Results, "Diffuser transmission function": Wiener deconvolution by the
-  // IOTF, zero-phase square root, back-propagation over L2
-  PWF_TRY(ew(pwf::PLAIN_FROM_REAL, nullptr, X));
-  PWF_TRY(filter(X, X, pwf::PLAIN_W_WIENER));
-  PWF_TRY(ew(pwf::PLAIN_SQRT_POS, X, X));
-  PWF_TRY(filter(X, t, pwf::PLAIN_W_Q2C));
+  // IOTF, zero-phase square root, back-propagation over L2, as five sweeps
+  // (one kernel per operation was twelve launches)
+  const Batch B = group(problem, 1);
+  const Launcher K{*ctx, ws, L, B, st};
+  PWF_TRY(K.row(pwf::ROW_REAL_FULL));
+  PWF_TRY(K.col(pwf::COL_WIENER));
+  PWF_TRY(K.row(pwf::ROW_SQRT_POS));
+  PWF_TRY(K.col(pwf::COL_CHIRP2_CONJ));
+  PWF_TRY(K.row(pwf::ROW_IFFT_OUT));
   return PWF_OK;
 }
 

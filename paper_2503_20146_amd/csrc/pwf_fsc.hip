@@ -302,28 +302,6 @@ __global__ void __launch_bounds__(kFscThreads) fsc_shell_kernel(const float4* __
   }
 }
 
-// out[j] = sum over workgroups of partial[b][j], 64 values per workgroup: each
-// of 16 waves sums every 16th row, then the waves' sums are added in order.
-// (One thread summing all rows is a chain of up to 768 loads: 0.23 ms.)
-constexpr int kFscFinalWaves = 16;
-__global__ void __launch_bounds__(64 * kFscFinalWaves) fsc_final_kernel(const double* __restrict__ partial, int blocks,
-                                                                        int len, double* __restrict__ out) {
-  __shared__ double red[kFscFinalWaves][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + lane;
-  double t = 0.0;
-  if (j < len) {
-#pragma unroll 8
-    for (int b = wave; b < blocks; b += kFscFinalWaves) t += partial[(size_t)b * len + j];
-  }
-  red[wave][lane] = t;
-  __syncthreads();
-  if (wave == 0 && j < len) {
-    for (int w = 1; w < kFscFinalWaves; ++w) t += red[w][lane];
-    out[j] = t;
-  }
-}
-
 template <int N>
 hipError_t fsc_run(const float2* g1, const float2* g2, int dims, int part, float s1, float s2, float2* X,
                    const float2* tw_row, const float2* tw_col, const float2* twn, double* partial, double* out,
@@ -350,10 +328,8 @@ hipError_t fsc_run(const float2* g1, const float2* g2, int dims, int part, float
     hipLaunchKernelGGL((fsc_shell_kernel<N, K, 3>), dim3(blocks), dim3(threads), lds, st, (const float4*)X, partial);
   else
     hipLaunchKernelGGL((fsc_shell_kernel<N, K, 2>), dim3(blocks), dim3(threads), lds, st, (const float4*)X, partial);
-  const int len = 3 * (H + 1);
-  hipLaunchKernelGGL(fsc_final_kernel, dim3((len + 63) / 64), dim3(64 * kFscFinalWaves), 0, st, partial, blocks, len,
-                     out);
-  return hipGetLastError();
+  if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  return launch_sum_rows(partial, blocks, 3 * (H + 1), out, st);
 }
 
 }  // namespace

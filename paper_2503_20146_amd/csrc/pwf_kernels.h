@@ -23,6 +23,8 @@ enum RowOp {
   ROW_CPLX_FFT,        // W = FFT_x(psi_src) (psi_src null: zeros)
   ROW_IFFT_OUT,        // out = IFFT_x(W)
   ROW_PSI_UPDATE_CORR, // S0 with the stopping rule's sums (runs with the plan of ROW_PSI_UPDATE)
+  ROW_REAL_FULL,       // W = FFT_x(y), all kx (ROW_REAL_FFT keeps the half form)
+  ROW_SQRT_POS,        // W = FFT_x(sqrt(max(Re IFFT_x(W), 0)))
 };
 
 // Row sweeps of the iteration (S0, S2, S4, S6, S8, S10) are compiled with every
@@ -51,6 +53,7 @@ enum ColOp {
   COL_DIRECTION,       // spectrum of the update direction d
   COL_SPEC_YHAT,       // y_hat = FFT_y(W)
   COL_SPEC_PSIHAT,     // psi_hat = FFT_y(W); z_hat = psi_hat
+  COL_WIENER,          // x IOTF / (IOTF^2 + wiener_eps) (calibration)
 };
 
 // Sweeps on the real intensity path work on x-spectra in half form: the
@@ -65,15 +68,12 @@ enum ColOp {
 constexpr bool col_op_half(int op) { return op == COL_BLUR_LOSS || op == COL_BLUR || op == COL_SPEC_YHAT; }
 
 enum PlainWindow {
-  PLAIN_W_Q1 = 0, PLAIN_W_Q2, PLAIN_W_Q2C, PLAIN_W_Q1C, PLAIN_W_IOTF, PLAIN_W_PINV, PLAIN_W_GAMMA2,
-  PLAIN_W_WIENER  // IOTF / (IOTF^2 + wiener_eps)
+  PLAIN_W_Q1 = 0, PLAIN_W_Q2, PLAIN_W_Q2C, PLAIN_W_Q1C, PLAIN_W_IOTF, PLAIN_W_PINV, PLAIN_W_GAMMA2
 };
 
 enum PlainOp {
   PLAIN_EXP = 0, PLAIN_MUL_T, PLAIN_MUL_CONJ_T, PLAIN_ABS2, PLAIN_REAL, PLAIN_NEG_ERR, PLAIN_MUL,
-  PLAIN_GRAD, PLAIN_IMAG, PLAIN_DIRECTION, PLAIN_NESTEROV,
-  PLAIN_FROM_REAL,  // out = (y, 0) from the descriptor's real image
-  PLAIN_SQRT_POS    // out = (sqrt(max(Re a, 0)), 0)
+  PLAIN_GRAD, PLAIN_IMAG, PLAIN_DIRECTION, PLAIN_NESTEROV
 };
 
 bool row_alt_default_n(int n, int op);
@@ -139,8 +139,10 @@ hipError_t launch_bg_subtract(float2* vol, int n_slices, int n, const double* pa
 // Calibration: FP64 partial sums, per workgroup, of sum I, sum I(x,y) I(x+d,y)
 // and sum I(x,y) I(x,y+d) for d = 0..max_shift (circular shifts), then their
 // ordered total -> out[0] = sum I, out[1 + d] = x-shift sum, out[2 + kMaxShift + d]
-// = y-shift sum (entries past max_shift are 0).  max_shift <= kMaxShift.
+// = y-shift sum (entries past max_shift are not meaningful).  max_shift <= kMaxShift.
 constexpr int kMaxShift = 32;
+// out[j] = sum over b < rows of partial[b * len + j], in a fixed order.
+hipError_t launch_sum_rows(const double* partial, int rows, int len, double* out, hipStream_t st);
 int speckle_sum_blocks();
 hipError_t launch_speckle_sums(const float* img, int nx, int ny, int max_shift, double* partial, double* out,
                                hipStream_t st);

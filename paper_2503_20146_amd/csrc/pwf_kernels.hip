@@ -35,11 +35,6 @@ __global__ void plain_window(float2* __restrict__ a, const Inst* __restrict__ ip
       case PLAIN_W_IOTF: val = cscale(val, iotf_at(I, kx, ky)); break;
       case PLAIN_W_PINV: val = cscale(val, pinv_of(I, fx, fy)); break;
       case PLAIN_W_GAMMA2: val = cscale(val, gamma2_at(I, kx, ky)); break;
-      case PLAIN_W_WIENER: {
-        const float h = iotf_at(I, kx, ky);
-        val = cscale(val, h / (h * h + I.wiener_eps));
-        break;
-      }
       default: break;
     }
     a[i] = cscale(val, I.inv_m);
@@ -74,8 +69,6 @@ __global__ void plain_elementwise(int op, size_t m, const float2* __restrict__ a
                              b[i].x + (I.alpha_c1 - I.alpha_c2) * c[i].y);
         break;
       }
-      case PLAIN_FROM_REAL: out[i] = make_float2(I.y[i], 0.f); break;
-      case PLAIN_SQRT_POS: out[i] = make_float2(sqrtf(fmaxf(a[i].x, 0.f)), 0.f); break;
       case PLAIN_NESTEROV: {  // a = psi (in/out via out), b = d, c = z (updated in place)
         const float bf = (float)beta[iter];
         const float2 zp = c[i];
@@ -472,54 +465,109 @@ hipError_t launch_joint_update(float* u1max, int n, int count, size_t max_stride
   return hipGetLastError();
 }
 
-// Speckle autocorrelation sums (Siegert calibration).  Each thread takes
-// pixels in a grid-stride loop and accumulates, for every shift d, the
-// products with the pixels d to the right and d below (circular), in FP64.
-__global__ void __launch_bounds__(256) speckle_sums_kernel(const float* __restrict__ img, int nx, int ny, int max_shift,
-                                    double* __restrict__ partial) {
-  constexpr int K = kMaxShift + 1;
-  constexpr int NV = 1 + 2 * K;
-  double acc[NV];  // [0]: sum I; [1 + d]: x shift d; [1 + K + d]: y shift d
+// Speckle autocorrelation sums (Siegert calibration): sum I, and for every
+// shift d the sums of I(x, y) I(x + d, y) and I(x, y) I(x, y + d) (circular),
+// in FP64 (the products too), in a fixed order.
+// A workgroup stages tiles of ROWS x 64 pixels and the kMaxShift pixels right
+// of and below them in LDS.  In a wave, lanes 0 .. 31 own the x shifts 1 .. 32
+// and lanes 32 .. 63 the y shifts: the wave walks the pixels of its rows, and
+// each lane multiplies the pixel (broadcast from the lane that holds its
+// column) by its own shifted one.  So a lane keeps one sum instead of 67, and
+// nothing is reduced across lanes but sum I and sum I^2.  Bound by the vector
+// ALU (four operations per pixel and wave).  With all 67 sums in every thread
+// the reductions and the one thread that added 512 partials of each sum were
+// 0.21 ms at 1024^2; 0.0SPK now.
+constexpr int kSpkCols = 64, kSpkPitch = kSpkCols + kMaxShift + 1;   // (odd: y lanes hit distinct banks)
+constexpr int kSpkValues = 1 + 2 * (kMaxShift + 1);
+
+template <int ROWS>
+__global__ void __launch_bounds__(256) speckle_sums_kernel(const float* __restrict__ img, int nx, int ny,
+                                                           int max_shift, double* __restrict__ partial) {
+  static_assert(kMaxShift == 32, "one lane per shift and axis");
+  __shared__ float tile[(ROWS + kMaxShift) * kSpkPitch];
+  __shared__ double red[4][66];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int d = (lane & 31) + 1;
+  const int off = lane < 32 ? d : d * kSpkPitch;
+  const int tx = (nx + kSpkCols - 1) / kSpkCols, ty = (ny + ROWS - 1) / ROWS;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0}, s1 = 0.0, s2 = 0.0;
+  for (int b = blockIdx.x; b < tx * ty; b += gridDim.x) {
+    const int y0 = (b / tx) * ROWS, x0 = (b % tx) * kSpkCols;
+    const int rows = min(ROWS, ny - y0), cols = min(kSpkCols, nx - x0);
+    const int wc = cols + max_shift, n = (rows + max_shift) * wc;   // staged: at most one wrap each way
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += 256) {
+      const int r = i / wc, c = i - r * wc;
+      int y = y0 + r, x = x0 + c;
+      y = y < ny ? y : y - ny;
+      x = x < nx ? x : x - nx;
+      tile[r * kSpkPitch + c] = img[(size_t)y * nx + x];
+    }
+    __syncthreads();
+    for (int r = wave; r < rows; r += 4) {
+      const float* t = tile + r * kSpkPitch;
+      const float v = lane < cols ? t[lane] : 0.f;
+      s1 += (double)v;
+      s2 = fma((double)v, (double)v, s2);
+      if (cols == kSpkCols && max_shift == kMaxShift) {
 #pragma unroll
-  for (int j = 0; j < NV; ++j) acc[j] = 0.0;
-  const size_t m = (size_t)nx * ny;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < m; i += (size_t)gridDim.x * blockDim.x) {
-    const int y = (int)(i / nx), x = (int)(i - (size_t)y * nx);
-    const float v = img[i];
-    acc[0] += v;
-#pragma unroll
-    for (int d = 0; d < K; ++d) {
-      if (d <= max_shift) {
-        const int xd = x + d < nx ? x + d : x + d - nx;
-        const int yd = y + d < ny ? y + d : y + d - ny;
-        acc[1 + d] += (double)(v * img[(size_t)y * nx + xd]);
-        acc[1 + K + d] += (double)(v * img[(size_t)yd * nx + x]);
+        for (int c = 0; c < kSpkCols; ++c) {
+          const double vc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), c));
+          acc[c & 3] = fma(vc, (double)t[c + off], acc[c & 3]);
+        }
+      } else if (d <= max_shift) {   // (lanes of shifts that were not asked for have nothing staged)
+        for (int c = 0; c < cols; ++c) acc[c & 3] = fma((double)t[c], (double)t[c + off], acc[c & 3]);
       }
     }
   }
-  // block reduction, one value at a time (wave butterflies, then waves in order)
-  __shared__ double red[16];
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    double a = acc[j];
-    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double t = 0.0;
-      for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += red[w];
-      partial[(size_t)blockIdx.x * NV + j] = t;
+  for (int o = 32; o > 0; o >>= 1) {
+    s1 += __shfl_xor(s1, o, 64);
+    s2 += __shfl_xor(s2, o, 64);
+  }
+  red[wave][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  if (lane == 0) {
+    red[wave][64] = s1;
+    red[wave][65] = s2;
+  }
+  __syncthreads();
+  if (threadIdx.x < 66) {
+    const int i = threadIdx.x;
+    const double t = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
+    double* p = partial + (size_t)blockIdx.x * kSpkValues;
+    if (i < 64) {
+      p[(i < 32 ? 1 : 2 + kMaxShift) + (i & 31) + 1] = t;
+    } else if (i == 64) {
+      p[0] = t;
+    } else {
+      p[1] = t;                 // d = 0 is the same sum on both axes
+      p[2 + kMaxShift] = t;
     }
-    __syncthreads();
   }
 }
 
-__global__ void speckle_sums_final(const double* __restrict__ partial, int blocks, int nv, double* __restrict__ out) {
-  for (int j = threadIdx.x; j < nv; j += blockDim.x) {
-    double t = 0.0;
-    for (int b = 0; b < blocks; ++b) t += partial[(size_t)b * nv + j];
+// out[j] = sum over rows b of partial[b][j], 64 values per workgroup: each of
+// 16 waves sums every 16th row, then the waves' sums are added in order.
+__global__ void __launch_bounds__(1024) sum_rows_kernel(const double* __restrict__ partial, int rows, int len,
+                                                        double* __restrict__ out) {
+  __shared__ double red[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = blockIdx.x * 64 + lane;
+  double t = 0.0;
+  if (j < len) {
+#pragma unroll 8
+    for (int b = wave; b < rows; b += 16) t += partial[(size_t)b * len + j];
+  }
+  red[wave][lane] = t;
+  __syncthreads();
+  if (wave == 0 && j < len) {
+    for (int w = 1; w < 16; ++w) t += red[w][lane];
     out[j] = t;
   }
+}
+
+hipError_t launch_sum_rows(const double* partial, int rows, int len, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(sum_rows_kernel, dim3((len + 63) / 64), dim3(1024), 0, st, partial, rows, len, out);
+  return hipGetLastError();
 }
 
 int speckle_sum_blocks() { return 512; }
@@ -527,11 +575,16 @@ int speckle_sum_blocks() { return 512; }
 hipError_t launch_speckle_sums(const float* img, int nx, int ny, int max_shift, double* partial, double* out,
                                hipStream_t st) {
   if (max_shift < 0 || max_shift > kMaxShift) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(speckle_sums_kernel, dim3(speckle_sum_blocks()), dim3(256), 0, st, img, nx, ny, max_shift,
-                     partial);
-  hipLaunchKernelGGL(speckle_sums_final, dim3(1), dim3(128), 0, st, partial, speckle_sum_blocks(),
-                     1 + 2 * (kMaxShift + 1), out);
-  return hipGetLastError();
+  // tiles of 32 rows where they fill the CUs, else of 16: twice the workgroups
+  const long tx = (nx + kSpkCols - 1) / kSpkCols;
+  const bool tall = tx * ((ny + 31) / 32) >= 256;
+  const long tiles = tx * ((ny + (tall ? 31 : 15)) / (tall ? 32 : 16));
+  const int blocks = (int)std::min<long>(tiles, speckle_sum_blocks());
+  if (tall)
+    hipLaunchKernelGGL(speckle_sums_kernel<32>, dim3(blocks), dim3(256), 0, st, img, nx, ny, max_shift, partial);
+  else
+    hipLaunchKernelGGL(speckle_sums_kernel<16>, dim3(blocks), dim3(256), 0, st, img, nx, ny, max_shift, partial);
+  return launch_sum_rows(partial, blocks, kSpkValues, out, st);
 }
 
 hipError_t launch_maxabs2_batch(const Maxabs2Batch& B, float* partial, hipStream_t st) {

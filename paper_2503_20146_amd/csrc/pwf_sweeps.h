@@ -49,6 +49,8 @@ PWF_ROW_TRAIT(ROW_FORWARD_OUT, true, false)
 PWF_ROW_TRAIT(ROW_REAL_FFT, false, true)
 PWF_ROW_TRAIT(ROW_CPLX_FFT, false, true)
 PWF_ROW_TRAIT(ROW_IFFT_OUT, true, false)
+PWF_ROW_TRAIT(ROW_REAL_FULL, false, true)
+PWF_ROW_TRAIT(ROW_SQRT_POS, true, true)
 #undef PWF_ROW_TRAIT
 
 // exp(p) for complex p.  The phase is reduced to a quadrant index n and a
@@ -356,7 +358,7 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
       if constexpr (PAIR) split_elements<false, PD, E>(v, wp, pb, [](auto i) { return decltype(i)::value; });
     }
     fft_inverse<Plan, T, WAVE>(v, t, twr, lv);
-  } else if constexpr (OP == ROW_REAL_FFT) {
+  } else if constexpr (OP == ROW_REAL_FFT || OP == ROW_REAL_FULL) {
     static_for<0, E / R1>([&](auto cc) {
       static_for<0, R1>([&](auto qq) {
         constexpr int c = decltype(cc)::value, q = decltype(qq)::value;
@@ -480,6 +482,8 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
       } else if constexpr (OP == ROW_FORWARD_OUT) {
         const float f = v[e].x;   // RMSE image (Methods): |y - f| scaled by 100 / <reference>
         gstf(I.f_out, idx, I.rmse_scale > 0.f ? fabsf(gldf(I.y, idx) - f) * I.rmse_scale : f);
+      } else if constexpr (OP == ROW_SQRT_POS) {
+        v[e] = make_float2(sqrtf(fmaxf(v[e].x, 0.f)), 0.f);
       } else if constexpr (OP == ROW_CPLX_FFT) {
         if (I.psi) gst(I.psi, idx, v[e]);
       } else if constexpr (OP == ROW_IFFT_OUT) {
@@ -603,6 +607,7 @@ PWF_COL_TRAIT(COL_CHIRP2_CONJ, true)
 PWF_COL_TRAIT(COL_CHIRP1_CONJ, true)
 PWF_COL_TRAIT(COL_BLUR_LOSS, true)
 PWF_COL_TRAIT(COL_BLUR, true)
+PWF_COL_TRAIT(COL_WIENER, true)
 PWF_COL_TRAIT(COL_NESTEROV, true)
 PWF_COL_TRAIT(COL_DIRECTION, true)
 PWF_COL_TRAIT(COL_SPEC_YHAT, false)
@@ -883,7 +888,7 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
     if constexpr (OP == COL_CHIRP1 || OP == COL_CHIRP1_CONJ) qx = gld(I.qx1, kx);
     if constexpr (OP == COL_CHIRP2 || OP == COL_CHIRP2_CONJ) qx = gld(I.qx2, kx);
     // (half form: the packed column 0 carries its x factors from the row sweeps)
-    if constexpr (OP == COL_BLUR || OP == COL_BLUR_LOSS) ixv = (HALF && s == 0) ? 1.f : gldf(I.ix, kx);
+    if constexpr (OP == COL_BLUR || OP == COL_BLUR_LOSS || OP == COL_WIENER) ixv = (HALF && s == 0) ? 1.f : gldf(I.ix, kx);
     // half form: columns s > 0 stand for kx and -kx in the loss
     const double wgt = (HALF && s > 0) ? 2.0 : 1.0;
     constexpr bool CHIRP = OP == COL_CHIRP1 || OP == COL_CHIRP1_CONJ || OP == COL_CHIRP2 || OP == COL_CHIRP2_CONJ;
@@ -929,6 +934,9 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
         const uint32_t o_e = (uint32_t)((part * NF + j) * nx + s);  // this element's place in the spectra
         if constexpr (OP == COL_BLUR) {
           v[e] = cscale(v[e], ixv * gldf(I.iy, ky) * I.inv_m);
+        } else if constexpr (OP == COL_WIENER) {
+          const float h = ixv * gldf(I.iy, ky);
+          v[e] = cscale(v[e], h / (h * h + I.wiener_eps) * I.inv_m);
         } else if constexpr (OP == COL_BLUR_LOSS) {
           const float h = ixv * ytab(j).x;
           const float2 yh = gld(I.y_hat, o_e);
@@ -1085,7 +1093,7 @@ hipError_t launch_row_np(int op, int plan, int nblocks, const Sweep& S, hipStrea
     PWF_TUNABLE(ROW_PSI_UPDATE) PWF_TUNABLE(ROW_PSI_UPDATE_CORR) PWF_TUNABLE(ROW_MUL_T) PWF_TUNABLE(ROW_MUL_CONJ_T) PWF_TUNABLE(ROW_INTENSITY)
     PWF_TUNABLE(ROW_BACKBLUR) PWF_TUNABLE(ROW_GRAD)
     PWF_FIXED(ROW_START) PWF_FIXED(ROW_FORWARD_OUT) PWF_FIXED(ROW_REAL_FFT) PWF_FIXED(ROW_CPLX_FFT)
-    PWF_FIXED(ROW_IFFT_OUT)
+    PWF_FIXED(ROW_IFFT_OUT) PWF_FIXED(ROW_REAL_FULL) PWF_FIXED(ROW_SQRT_POS)
 #undef PWF_TUNABLE
 #undef PWF_FIXED
     default: return hipErrorInvalidValue;
@@ -1108,7 +1116,7 @@ hipError_t launch_col_nw(int op, int nblocks, const Sweep& S, hipStream_t st) {
 #define PWF_CASE(o) case o: hipLaunchKernelGGL((col_sweep<N, W, o>), grid, block, 0, st, S); break;
     PWF_CASE(COL_CHIRP1) PWF_CASE(COL_CHIRP2) PWF_CASE(COL_CHIRP2_CONJ) PWF_CASE(COL_CHIRP1_CONJ)
     PWF_CASE(COL_BLUR_LOSS) PWF_CASE(COL_BLUR) PWF_CASE(COL_NESTEROV) PWF_CASE(COL_DIRECTION)
-    PWF_CASE(COL_SPEC_YHAT) PWF_CASE(COL_SPEC_PSIHAT)
+    PWF_CASE(COL_SPEC_YHAT) PWF_CASE(COL_SPEC_PSIHAT) PWF_CASE(COL_WIENER)
 #undef PWF_CASE
     default: return hipErrorInvalidValue;
   }
