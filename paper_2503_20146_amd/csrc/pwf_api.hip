@@ -119,6 +119,19 @@ int row_plan(int n, int op) {
   return g_row_plan[i][op];
 }
 
+// Plan and tile width that a class of `count` instances runs with: what was set
+// (by the caller or the autotuner), else the latency plan where it applies,
+// else the built-in choice.
+int class_row_plan(int nx, int ny, int count, int op) {
+  if (op == pwf::ROW_PSI_UPDATE_CORR) op = pwf::ROW_PSI_UPDATE;
+  const bool set = pwf::row_plan_tunable(op) && g_row_plan[size_index(nx)][op] >= 0;
+  return !set && pwf::latency_shape(nx, ny, count) ? 2 : row_plan(nx, op);
+}
+int class_col_width(int nx, int ny, int count, int op) {
+  const bool set = g_col_width[size_index(ny)][op] != 0;
+  return !set && pwf::latency_shape(nx, ny, count) ? pwf::kLatencyWidth : col_width(ny, op);
+}
+
 // Row op of iteration sweep S0, S2, ..., S10 (-1 for other indices).
 int row_op_of_sweep(int sweep) {
   switch (sweep) {
@@ -300,11 +313,12 @@ int col_blocks(int nx, int ny, int op, int width) {
   return (pwf::col_op_half(op) ? nx / 2 : nx) / width * (pwf::col_split_n(ny) ? 2 : 1);
 }
 // loss partials: one per workgroup of the residual sweep
-int n_partials(const pwf_problem& p) {
-  return col_blocks(p.geom.nx, p.geom.ny, pwf::COL_BLUR_LOSS, col_width(p.geom.ny, pwf::COL_BLUR_LOSS));
+int n_partials(int nx, int ny, int count) {
+  return col_blocks(nx, ny, pwf::COL_BLUR_LOSS, class_col_width(nx, ny, count, pwf::COL_BLUR_LOSS));
 }
 // room for per-workgroup partials of a column sweep at the narrowest compiled tile
 int max_partials(const pwf_problem& p) {
+  // (the residual sweep's latency tiles, half as wide, cover half the columns)
   const int narrow = std::min(pwf::col_default_width(p.geom.ny), pwf::col_alt_width(p.geom.ny));
   return col_blocks(p.geom.nx, p.geom.ny, pwf::COL_CHIRP1, narrow);
 }
@@ -321,8 +335,19 @@ struct Layout {
   size_t total = 0;
 };
 
+// Batch order: the instances of a grid shape together (see group()), so that
+// their fields lie one after the other.
+std::vector<int> batch_order(const pwf_problem* probs, int n) {
+  std::vector<int> order(n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
+    return std::make_pair(probs[a].geom.ny, probs[a].geom.nx) < std::make_pair(probs[c].geom.ny, probs[c].geom.nx);
+  });
+  return order;
+}
+
 // Region order keeps W, psi_hat and z_hat of all instances contiguous so that
-// one fill kernel clears them.
+// one fill kernel clears them; within a region the fields follow batch order.
 Layout make_layout(const pwf_problem* probs, int n, bool joint = false) {
   Layout L;
   size_t off = 0;
@@ -353,9 +378,10 @@ Layout make_layout(const pwf_problem* probs, int n, bool joint = false) {
   }
   L.stop = off;
   off += align_up(sizeof(int32_t) * n);
+  const std::vector<int> order = batch_order(probs, n);
   auto region = [&](std::vector<size_t>& r) {
     r.resize(n);
-    for (int i = 0; i < n; ++i) {
+    for (int i : order) {
       r[i] = off;
       off += field_bytes(probs[i]);
     }
@@ -407,9 +433,10 @@ Layout make_loss_grad_layout(const pwf_problem* probs, int n) {
     L.tables[i] = off;
     off += table_bytes(probs[i]);
   }
+  const std::vector<int> order = batch_order(probs, n);
   for (std::vector<size_t>* r : {&L.W, &L.v, &L.psi, &L.y_hat}) {
     r->resize(n);
-    for (int i = 0; i < n; ++i) {
+    for (int i : order) {
       (*r)[i] = off;
       off += field_bytes(probs[i]);
     }
@@ -420,13 +447,14 @@ Layout make_loss_grad_layout(const pwf_problem* probs, int n) {
 
 // ------------------------------------------------------------------ descriptors
 
-Inst base_inst(const pwf_problem& p) {
+// (count: instances of this grid shape in the batch)
+Inst base_inst(const pwf_problem& p, int count) {
   Inst I;
   std::memset(&I, 0, sizeof(I));
   const pwf_geometry& g = p.geom;
   I.nx = g.nx;
   I.ny = g.ny;
-  I.n_partials = n_partials(p);
+  I.n_partials = n_partials(g.nx, g.ny, count);
   I.t = (const float2*)p.diffuser;
   const double p2 = g.pixel_m * g.pixel_m;
   I.chirp1_rev = g.z1_m * g.wavelength_m / (2.0 * p2);
@@ -495,15 +523,16 @@ struct Class {
 struct Batch {
   std::vector<int> order;  // descriptor slot -> caller index
   std::vector<Class> classes;
+  int count(const pwf_problem& p) const {   // instances of p's grid shape
+    for (const Class& c : classes)
+      if (c.nx == p.geom.nx && c.ny == p.geom.ny) return c.count;
+    return 0;
+  }
 };
 
 Batch group(const pwf_problem* probs, int n) {
   Batch b;
-  b.order.resize(n);
-  for (int i = 0; i < n; ++i) b.order[i] = i;
-  std::stable_sort(b.order.begin(), b.order.end(), [&](int a, int c) {
-    return std::make_pair(probs[a].geom.ny, probs[a].geom.nx) < std::make_pair(probs[c].geom.ny, probs[c].geom.nx);
-  });
+  b.order = batch_order(probs, n);
   for (int s = 0; s < n;) {
     const pwf_problem& p = probs[b.order[s]];
     int e = s;
@@ -536,10 +565,8 @@ struct Launcher {
   hipStream_t st;
   double corr_tol = 0.0;
   bool merged = false;   // batch_merged(B): one launch per sweep over the classes
-  int width_of(int ny, int op) const { return col_width(ny, op); }
-  int plan_of(int nx, int op) const {
-    return row_plan(nx, op == pwf::ROW_PSI_UPDATE_CORR ? (int)pwf::ROW_PSI_UPDATE : op);
-  }
+  int width_of(const Class& c, int op) const { return class_col_width(c.nx, c.ny, c.count, op); }
+  int plan_of(const Class& c, int op) const { return class_row_plan(c.nx, c.ny, c.count, op); }
   Inst* dev_desc() const { return (Inst*)(ws + L.desc); }
   int32_t* status() const { return (int32_t*)(ws + L.status); }
 
@@ -560,15 +587,24 @@ struct Launcher {
     S.twn_pair = ctx.twn[size_index(c.ny)];
     S.pair_half = split ? c.ny / 2 : 0;
     S.status = status();
-    S.blocks_per_inst = 0;
+    S.W = (float2*)(ws + L.W[B.order[c.first]]);
+    S.field = c.nx * c.ny;
+    S.nx = c.nx;
+    S.stopping = corr_tol > 0.0 ? 1 : 0;
+    S.blocks_per_inst = S.lg_blocks = 0;
     S.corr_tol = corr_tol;
     return S;
+  }
+  // (blocks per instance: the sides, tile widths and rows per workgroup are powers of two)
+  static void set_blocks(Sweep& S, int blocks) {
+    S.blocks_per_inst = blocks;
+    S.lg_blocks = __builtin_ctz((unsigned)blocks);
   }
   pwf_status row(int op, int iter = 0) const {
     for (const Class& c : B.classes) {
       Sweep S = sweep(c, iter);
-      const int plan = plan_of(c.nx, op);
-      S.blocks_per_inst = c.ny / pwf::row_rows_per_block(c.nx, plan);
+      const int plan = plan_of(c, op);
+      set_blocks(S, c.ny / pwf::row_rows_per_block(c.nx, plan));
       PWF_HIP(pwf::launch_row(c.nx, op, plan, S.blocks_per_inst * c.count, S, st));
     }
     return PWF_OK;
@@ -576,8 +612,9 @@ struct Launcher {
   pwf_status col(int op, int iter = 0) const {
     for (const Class& c : B.classes) {
       Sweep S = sweep(c, iter);
-      const int width = width_of(c.ny, op);
-      S.blocks_per_inst = col_blocks(c.nx, c.ny, op, width);
+      const int width = width_of(c, op);
+      if (c.ny <= 256 && width == pwf::kLatencyWidth) S.tw_col = ctx.twa2[size_index(c.ny)];   // its plan is the rows' third
+      set_blocks(S, col_blocks(c.nx, c.ny, op, width));
       PWF_HIP(pwf::launch_col(c.ny, width, op, S.blocks_per_inst * c.count, S, st));
     }
     return PWF_OK;
@@ -589,9 +626,9 @@ struct Launcher {
     std::memset(&M, 0, sizeof(M));
     int total = 0, m = 0;
     for (const Class& c : B.classes) {
-      const int plan = plan_of(c.nx, op);
+      const int plan = plan_of(c, op);
       Sweep S = sweep(c, iter);
-      S.blocks_per_inst = c.ny / pwf::row_rows_per_block(c.nx, plan);
+      set_blocks(S, c.ny / pwf::row_rows_per_block(c.nx, plan));
       if (!pwf::multi_row_supported(c.nx, c.ny, plan) || m == pwf::kMaxMerged) {
         PWF_HIP(pwf::launch_row(c.nx, op, plan, S.blocks_per_inst * c.count, S, st));
         continue;
@@ -614,9 +651,9 @@ struct Launcher {
     std::memset(&M, 0, sizeof(M));
     int total = 0, m = 0;
     for (const Class& c : B.classes) {
-      const int width = width_of(c.ny, op);
+      const int width = width_of(c, op);
       Sweep S = sweep(c, iter);
-      S.blocks_per_inst = col_blocks(c.nx, c.ny, op, width);
+      set_blocks(S, col_blocks(c.nx, c.ny, op, width));
       if (width != pwf::multi_col_width(c.ny) || m == pwf::kMaxMerged) {
         PWF_HIP(pwf::launch_col(c.ny, width, op, S.blocks_per_inst * c.count, S, st));
         continue;
@@ -742,7 +779,7 @@ pwf_status forward_impl(const pwf_problem* problems, int32_t n, const void* cons
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i]);
+    I = base_inst(problems[i], B.count(problems[i]));
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.psi_src = (const float2*)psi[i];
@@ -783,7 +820,7 @@ void loss_grad_descriptors(const pwf_problem* problems, int32_t n, const Batch& 
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i]);
+    I = base_inst(problems[i], B.count(problems[i]));
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -857,7 +894,7 @@ pwf_status pwf_gradient(const pwf_problem* problems, int32_t n, const void* cons
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i]);
+    I = base_inst(problems[i], B.count(problems[i]));
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -943,7 +980,7 @@ pwf_status pwf_state_init(const pwf_problem* problems, int32_t n, pwf_state* sta
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i]);
+    I = base_inst(problems[i], B.count(problems[i]));
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.y = y[i];
@@ -985,7 +1022,7 @@ pwf_status pwf_step(const pwf_problem* problems, int32_t n, pwf_state* states, d
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i]);
+    I = base_inst(problems[i], B.count(problems[i]));
     attach_tables(I, ws, L, i);
     I.k0 = states[i].k;
     I.W = (float2*)(ws + L.W[i]);
@@ -1038,7 +1075,7 @@ struct JointCfg {
 pwf_status joint_step(const Launcher& K, const pwf_problem* probs, int n, const JointCfg& jc) {
   const pwf_problem& p = probs[0];
   const size_t m = (size_t)p.geom.nx * p.geom.ny;
-  const int count = p.geom.ny / pwf::row_rows_per_block(p.geom.nx, row_plan(p.geom.nx, pwf::ROW_MUL_T));
+  const int count = p.geom.ny / pwf::row_rows_per_block(p.geom.nx, class_row_plan(p.geom.nx, p.geom.ny, n, pwf::ROW_MUL_T));
   float2* t = (float2*)p.diffuser;
   PWF_HIP(pwf::launch_joint_update((float*)(K.ws + K.L.u1max), n, count, (size_t)p.geom.ny,
                                    (const float2*)(K.ws + K.L.u1[0]), field_bytes(p) / sizeof(float2), m, t,
@@ -1055,7 +1092,7 @@ pwf_status solve_sequence(const Launcher& K, const pwf_problem* probs, int n, st
   PWF_TRY(K.row(pwf::ROW_REAL_FFT));
   PWF_TRY(K.col(pwf::COL_SPEC_YHAT));
   PWF_HIP(pwf::launch_fill_zero(K.ws + K.L.status, 16, K.st));
-  PWF_HIP(pwf::launch_fill_zero(K.ws + K.L.W[0], K.L.v[0] - K.L.W[0], K.st));
+  PWF_HIP(pwf::launch_fill_zero(K.ws + K.L.W[K.B.order[0]], K.L.v[K.B.order[0]] - K.L.W[K.B.order[0]], K.st));
   const int s0 = K.corr_tol > 0.0 ? pwf::ROW_PSI_UPDATE_CORR : pwf::ROW_PSI_UPDATE;
   auto iterate = [&](const Launcher& Q) -> pwf_status {
     for (int k = 0; k < iters; ++k) {
@@ -1151,7 +1188,7 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i]);
+    I = base_inst(problems[i], B.count(problems[i]));
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -1170,7 +1207,9 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
     if (corr_mode) {
       I.corr_partial = (double*)(ws + L.corr[i]);
       I.n_corr_partials = problems[i].geom.ny /
-                          pwf::row_rows_per_block(problems[i].geom.nx, row_plan(problems[i].geom.nx, pwf::ROW_PSI_UPDATE));
+                          pwf::row_rows_per_block(problems[i].geom.nx,
+                                                  class_row_plan(problems[i].geom.nx, problems[i].geom.ny,
+                                                                 B.count(problems[i]), pwf::ROW_PSI_UPDATE));
       I.stop_iter = (int32_t*)(ws + L.stop) + i;
     }
   }
@@ -1314,7 +1353,7 @@ pwf_status pwf_bench_sweep(const pwf_problem* problems, int32_t n, int32_t sweep
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i]);
+    I = base_inst(problems[i], B.count(problems[i]));
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -1406,7 +1445,7 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i]);
+    I = base_inst(problems[i], B.count(problems[i]));
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -1420,7 +1459,7 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
   PWF_TRY(upload(*ctx, desc.data(), sizeof(Inst) * n, ws + L.desc, st));
   PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
   // every field region (timing does not depend on the values)
-  PWF_HIP(pwf::launch_fill_zero(ws + L.W[0], L.extra0[0] - L.W[0], st));
+  PWF_HIP(pwf::launch_fill_zero(ws + L.W[B.order[0]], L.extra0[0] - L.W[B.order[0]], st));
   hipEvent_t e0, e1;
   PWF_HIP(hipEventCreate(&e0));
   PWF_HIP(hipEventCreate(&e1));
@@ -1432,6 +1471,13 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
     one.classes = {c};
     const Launcher K{*ctx, ws, L, one, st};
     const int cidx = size_index(c.ny), ridx = size_index(c.nx);
+    if (pwf::latency_shape(c.nx, c.ny, c.count)) {   // the latency plan, where nothing is set
+      for (int sweep = 0; sweep < 12; ++sweep) {
+        if (sweep & 1) g_col_width[cidx][col_op_of_sweep(sweep)] = 0;
+        else g_row_plan[ridx][row_op_of_sweep(sweep)] = -1;
+      }
+      continue;
+    }
     // time `reps` launches of one sweep (after a warm-up launch)
     auto timed = [&](auto launch, float* ms) -> pwf_status {
       PWF_TRY(launch());
@@ -1530,9 +1576,10 @@ std::vector<int> batch_sides(const Batch& B) {
 
 std::string tuning_line(const std::string& arch, const std::string& mix, int side) {
   std::string l = arch + ' ' + mix + ' ' + std::to_string(side) + " c";
-  for (int sw = 1; sw < 12; sw += 2) l += ' ' + std::to_string(col_width(side, col_op_of_sweep(sw)));
+  // (0 and -1: the built-in choice)
+  for (int sw = 1; sw < 12; sw += 2) l += ' ' + std::to_string(g_col_width[size_index(side)][col_op_of_sweep(sw)]);
   l += " r";
-  for (int sw = 0; sw < 12; sw += 2) l += ' ' + std::to_string(row_plan(side, row_op_of_sweep(sw)));
+  for (int sw = 0; sw < 12; sw += 2) l += ' ' + std::to_string(g_row_plan[size_index(side)][row_op_of_sweep(sw)]);
   return l;
 }
 
@@ -1551,7 +1598,8 @@ int apply_tuning_line(const std::string& line, const std::string& arch, const st
   const int i = size_index(side);
   if (i < 0) return 0;
   for (int k = 0; k < 6; ++k) {
-    if (!pwf::col_width_supported(side, w[k]) || pl[k] < 0 || pl[k] >= pwf::row_plan_count_n(side)) return 0;
+    if ((w[k] != 0 && !pwf::col_width_supported(side, w[k])) || pl[k] < -1 || pl[k] >= pwf::row_plan_count_n(side))
+      return 0;
   }
   for (int k = 0; k < 6; ++k) {
     g_col_width[i][col_op_of_sweep(2 * k + 1)] = w[k];
@@ -1640,7 +1688,7 @@ pwf_status pwf_solve_plain(const pwf_problem* problem, const float* y, void* psi
   const pwf_problem& p = *problem;
   const int nx = p.geom.nx, ny = p.geom.ny;
   const size_t m = (size_t)nx * ny;
-  Inst I = base_inst(p);
+  Inst I = base_inst(p, 1);
   attach_tables(I, ws, L, 0);
   I.y = y;
   I.maxt2 = (const float*)(ws + L.maxt2);
@@ -1772,7 +1820,7 @@ pwf_status pwf_diffuser_from_reference(const pwf_problem* problem, const float* 
   PWF_TRY(context_for_current(&ctx));
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  Inst I = base_inst(*problem);
+  Inst I = base_inst(*problem, 1);
   attach_tables(I, ws, L, 0);
   I.W = (float2*)(ws + L.W[0]);
   I.y = ref;

@@ -18,7 +18,7 @@ struct Inst {
   int32_t nx, ny;
   int32_t k0;           // iterations already done (momentum table offset)
   int32_t n_partials;   // number of loss partials (column tiles)
-  float2* W;            // work field between sweeps
+  float2* W;            // work field between sweeps (the sweeps take it from Sweep::W)
   float2* v;            // detector field v, saved by the forward for the gradient
   float2* u1;           // joint diffuser mode: field incident on the diffuser (S2), then
                         // conj(u1) a2 (S8); null otherwise
@@ -182,7 +182,10 @@ template <> struct RowCfgAlt<1024> { using Plan = FftPlan<1024, 16, 16, 4>; stat
 template <> struct RowCfgAlt<2048> { using Plan = FftPlan<2048, 16, 16, 8>; static constexpr int T = 128, RW = 2; };
 // A third plan on the large sides: the alternative plan's radices in the other
 // order (small radix first), searched by the autotuner.
+// On the small sides it is the plan of latency-bound batches (latency_shape).
 template <int N> struct RowCfgAlt2 : RowCfg<N> {};
+template <> struct RowCfgAlt2<128>  { using Plan = FftPlan<128, 4, 4, 4, 2>;  static constexpr int T = 32,  RW = 8; };
+template <> struct RowCfgAlt2<256>  { using Plan = FftPlan<256, 4, 4, 4, 4>;  static constexpr int T = 64,  RW = 4; };
 template <> struct RowCfgAlt2<1024> { using Plan = FftPlan<1024, 4, 16, 16>; static constexpr int T = 64,  RW = 4; };
 template <> struct RowCfgAlt2<2048> { using Plan = FftPlan<2048, 8, 16, 16>; static constexpr int T = 128, RW = 2; };
 template <int N> constexpr int row_plan_count() { return (N == 1024 || N == 2048) ? 3 : 2; }
@@ -202,6 +205,27 @@ template <> struct ColCfg<256>  { using Plan = FftPlan<256, 16, 16>;     static 
 template <> struct ColCfg<512>  { using Plan = FftPlan<512, 16, 8, 4>;   static constexpr int T = 32,  WA = 16, WB = 8; };
 template <> struct ColCfg<1024> { using Plan = FftPlan<1024, 16, 16, 4>; static constexpr int T = 64,  WA = 8,  WB = 16; };
 template <> struct ColCfg<2048> { using Plan = FftPlan<2048, 16, 16, 8>; static constexpr int T = 128, WA = 4,  WB = 8; };
+
+// Column configuration by tile width: 8-column tiles of 128- and 256-point
+// columns are those of latency-bound batches, with the row plans' four elements
+// per lane.
+constexpr int kLatencyWidth = 8;
+template <int N, int W> struct ColPlanSel : ColCfg<N> {};
+template <> struct ColPlanSel<128, kLatencyWidth> { using Plan = FftPlan<128, 4, 4, 4, 2>; static constexpr int T = 32; };
+template <> struct ColPlanSel<256, kLatencyWidth> { using Plan = FftPlan<256, 4, 4, 4, 4>; static constexpr int T = 64; };
+
+// Batches that do not fill the chip on small grids: a wave's own chain of
+// arithmetic and LDS exchanges is then the time of a sweep, not the memory.
+// At 16 elements per lane a 128^2 field is 16 waves of ~1500 operations each;
+// four elements per lane make it 64 waves of a third of that, for two more LDS
+// exchanges: 82 -> 58 us an iteration for one field of 128^2, 109 -> 96 for 64
+// (row sweeps alone), while 256 of them, bound by memory, ran 2% slower.
+// Both sides are at most 256: on larger grids the preconditioner amplifies the
+// rounding differences between the plans, and fields fill more of the chip.
+constexpr int kLatencyPixels = 1 << 20;
+constexpr bool latency_shape(int nx, int ny, int count) {
+  return nx <= 256 && ny <= 256 && (long long)nx * ny * count <= kLatencyPixels;
+}
 
 // Radix-2 split of the column transforms of the sweeps on sides of 512 and
 // more.  A 2048-point column needs 16 KB of LDS, so a tile of 8 columns
@@ -240,7 +264,14 @@ template <int NY> using ColSweepCfg = ColCfg<col_fft_len<NY>()>;
 // Arguments common to every sweep launch.
 struct Sweep {
   const Inst* inst;       // device array of descriptors
-  int32_t blocks_per_inst;
+  // What a workgroup needs to issue its loads of W, without a round trip to the
+  // descriptor first: the class's work fields lie one after the other.
+  float2* W;              // work field of the class's first instance
+  int32_t field;          // elements of a field, nx ny
+  int32_t nx;
+  int32_t blocks_per_inst;  // a power of two
+  int32_t lg_blocks;        // its logarithm
+  int32_t stopping;       // 1: the stopping rule is on (instances may have stopped)
   int32_t iter;           // iteration index within this call
   const double* beta;     // momentum table (Algorithm S1), indexed by k0 + iter
   const float2* tw_row;   // twiddles of the row plan (forward, then reversed plan)
@@ -268,8 +299,12 @@ struct MultiSweep {
 };
 
 // True when the instance has met the correlation stop: its sweeps are skipped.
-__device__ __forceinline__ bool instance_stopped(const Inst& I) {
-  return I.stop_iter != nullptr && *(volatile const int32_t*)I.stop_iter != 0;
+// (Only asked when the launch carries Sweep::stopping: the answer costs a round
+// trip to the descriptor before the first load.)
+__device__ __forceinline__ bool instance_stopped(const Inst* I) {
+  // (volatile: not read ahead of the condition on Sweep::stopping)
+  const volatile int32_t* const p = *(int32_t* const volatile*)&I->stop_iter;
+  return p != nullptr && *p != 0;
 }
 
 }  // namespace pwf

@@ -377,8 +377,12 @@ __device__ __forceinline__ void exchange_sync() {
 // + q N/R0]) -> registers in "last-radix layout" (v[c*RL + r] = X[t + T c + r
 // N/RL]).  The LDS region must be free on entry; it is free again on exit
 // (a trailing barrier is issued only between passes).
-template <class Plan, int T, bool WAVE = false, int E, class TW>
-__device__ __forceinline__ void fft_forward(float2 (&v)[E], int t, const TW& tw, LdsView lds) {
+// `mid` runs between the first pass's arithmetic and its LDS exchange.
+struct FftNoMid {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <class Plan, int T, bool WAVE = false, int E, class TW, class MID = FftNoMid>
+__device__ __forceinline__ void fft_forward(float2 (&v)[E], int t, const TW& tw, LdsView lds, MID mid = MID{}) {
   static_for<0, Plan::NPASS>([&](auto pp) {
     constexpr int P = decltype(pp)::value;
     if constexpr (P > 0) {
@@ -386,6 +390,7 @@ __device__ __forceinline__ void fft_forward(float2 (&v)[E], int t, const TW& tw,
       exchange_sync<WAVE>();
     }
     pass_compute<Plan, P, T, -1>(v, t, tw);
+    if constexpr (P == 0) mid();
     if constexpr (P + 1 < Plan::NPASS) {
       pass_store_lds<Plan, P, T>(v, t, lds);
       exchange_sync<WAVE>();

@@ -165,7 +165,9 @@ struct TwStage {
     static_for<0, K>([&](auto jj) {
       constexpr int j = decltype(jj)::value;
       const int i = (int)threadIdx.x + j * NTHR;
-      if (COUNT % NTHR == 0 || i < COUNT) r[j] = gld(src, (uint32_t)i);
+      // (a clamped index, not a condition: behind one the compiler waits for the
+      // load before it issues the next)
+      r[j] = gld(src, (uint32_t)(COUNT % NTHR == 0 || i < COUNT ? i : COUNT - 1));
     });
   }
   __device__ __forceinline__ void store(float2* lds) const {
@@ -242,10 +244,11 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
   constexpr int M1 = NX / R1, ML = NX / RL;
   constexpr bool IN_FREQ = RowOpTraits<OP>::kInFreq, OUT_FREQ = RowOpTraits<OP>::kOutFreq;
 
-  const int inst = b / S.blocks_per_inst;
-  const int blk = b - inst * S.blocks_per_inst;
-  const Inst I = S.inst[inst];  // by value: the fields stay in registers
-  if (instance_stopped(I)) return;  // uniform over the workgroup
+  const int inst = b >> S.lg_blocks;
+  const int blk = b - (inst << S.lg_blocks);
+  float2* const __restrict__ W = S.W + (size_t)inst * S.field;
+  const Inst* const ip = S.inst + inst;
+  if (S.stopping && instance_stopped(ip)) return;  // uniform over the workgroup
   // Rows of the workgroup: RW consecutive rows, or, with the column transform
   // split (PAIR, pair_half = H = ny/2), RW/2 pairs (n, n + H) whose two rows
   // sit PD lanes apart in one wave (lane t of row n + H is PD lanes after lane
@@ -285,6 +288,28 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
   // LDS exchange orders these writes before the first use.
   TwStage<TS::kLds, row_threads<NX, PLAN>()> tws;
   if constexpr (TS::kMode != 0) tws.load(TS::staged_from(twg, S.twn_row));
+  // The loads of W go out before the descriptor is read: they need only the
+  // launch's arguments, and the descriptor's round trip (and the addresses of
+  // the other fields in it) then passes while they are on their way.
+  float2 v[E];
+  constexpr bool IN_HALF = OP == ROW_BACKBLUR || OP == ROW_FORWARD_OUT;
+  if constexpr (IN_FREQ) {
+    static_for<0, E / RL>([&](auto cc) {
+      static_for<0, RL>([&](auto rr) {
+        constexpr int c = decltype(cc)::value, r = decltype(rr)::value;
+        const int kx = t + T * c + r * ML;
+        if constexpr (IN_HALF) {
+          // half-form x-spectrum (see col_op_half): kx > nx/2 from conj at nx - kx,
+          // kx = 0 and nx/2 from the packed position 0
+          const int kk = kx <= NX / 2 ? kx : NX - kx;
+          v[c * RL + r] = gld(W, wbase + (uint32_t)(kk == NX / 2 ? 0 : kk));
+        } else {
+          v[c * RL + r] = gld(W, wbase + col_of_kx(kx, NX));
+        }
+      });
+    });
+  }
+  const Inst I = *ip;  // by value: the fields stay in registers
   // The transforms of a row (or of a pair of rows) whose lanes lie in one wave
   // order their LDS exchanges per wave; the staged twiddles, which every wave
   // reads, then need a workgroup barrier of their own.
@@ -303,22 +328,10 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
   constexpr bool SIDE = OP == ROW_MUL_T || OP == ROW_MUL_CONJ_T || OP == ROW_BACKBLUR ||
                         (OP == ROW_GRAD && E <= 16);
   float2 side[SIDE ? E : 1];
-  float2 v[E];
   if constexpr (IN_FREQ) {
-    if constexpr (OP == ROW_BACKBLUR || OP == ROW_FORWARD_OUT) {
-      // half-form x-spectrum (see col_op_half): kx > nx/2 from conj at nx - kx,
-      // kx = 0 and nx/2 from the packed position 0 (after the residual sweep's
-      // second IOTF, kx = nx/2 still lacks its second x factor)
-      const uint32_t rh = wbase;
+    if constexpr (IN_HALF) {
+      // (after the residual sweep's second IOTF, kx = nx/2 still lacks its second x factor)
       const float s_ny = OP == ROW_BACKBLUR ? gldf(I.ix, NX / 2) : 1.f;
-      static_for<0, E / RL>([&](auto cc) {
-        static_for<0, RL>([&](auto rr) {
-          constexpr int c = decltype(cc)::value, r = decltype(rr)::value;
-          const int kx = t + T * c + r * ML;
-          const int kk = kx <= NX / 2 ? kx : NX - kx;
-          v[c * RL + r] = gld(I.W, rh + (uint32_t)(kk == NX / 2 ? 0 : kk));
-        });
-      });
       // the split's butterflies act on the stored values (the packed column
       // included), before they are unpacked
       if constexpr (PAIR) split_elements<false, PD, E>(v, wp, pb, [](auto i) { return decltype(i)::value; });
@@ -331,13 +344,6 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
           else if (kx == 0) a.y = 0.f;
           else if (kx == NX / 2) a = make_float2(s_ny * a.y, 0.f);
           v[c * RL + r] = a;
-        });
-      });
-    } else {
-      static_for<0, E / RL>([&](auto cc) {
-        static_for<0, RL>([&](auto rr) {
-          constexpr int c = decltype(cc)::value, r = decltype(rr)::value;
-          v[c * RL + r] = gld(I.W, wbase + col_of_kx(t + T * c + r * ML, NX));
         });
       });
     }
@@ -353,7 +359,7 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
         });
       });
     }
-    if constexpr (!(OP == ROW_BACKBLUR || OP == ROW_FORWARD_OUT)) {
+    if constexpr (!IN_HALF) {
       // (issued after the side loads, whose latency then overlaps the wait)
       if constexpr (PAIR) split_elements<false, PD, E>(v, wp, pb, [](auto i) { return decltype(i)::value; });
     }
@@ -514,17 +520,17 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
         static_for<0, RL / 2>([&](auto rr) {
           constexpr int c = decltype(cc)::value, r = decltype(rr)::value;
           const int kx = t + T * c + r * ML;
-          if (kx > 0) gst(I.W, rh + (uint32_t)kx, v[c * RL + r]);
+          if (kx > 0) gst(W, rh + (uint32_t)kx, v[c * RL + r]);
         });
       });
-      if (t == 0) gst(I.W, rh, packed);
+      if (t == 0) gst(W, rh, packed);
     } else {
       if constexpr (PAIR) split_elements<true, PD, E>(v, wp, pb, [](auto i) { return decltype(i)::value; });
       const uint32_t rb_st = opaque(wbase);
       static_for<0, E / RL>([&](auto cc) {
         static_for<0, RL>([&](auto rr) {
           constexpr int c = decltype(cc)::value, r = decltype(rr)::value;
-          gst(I.W, rb_st + col_of_kx(t + T * c + r * ML, NX), v[c * RL + r]);
+          gst(W, rb_st + col_of_kx(t + T * c + r * ML, NX), v[c * RL + r]);
         });
       });
     }
@@ -649,7 +655,7 @@ template <int NY, int W, int OP> constexpr int col_min_waves() {
 template <int NY, int W>
 struct ColLds {
   static constexpr int NF = col_fft_len<NY>();
-  using TS = TwSel<typename ColCfg<NF>::Plan, 1, true>;
+  using TS = TwSel<typename ColPlanSel<NF, W>::Plan, 1, true>;
   static constexpr int kExchange = W * lds_len(NF);
   static constexpr int kTwiddles = TS::kLds;
   static constexpr int kYTable = NF / 2 + 1;  // chirp sweeps: staged y factors
@@ -671,7 +677,7 @@ template <int NY, int W, int OP>
 __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, float2* twl, float2* qyl) {
   constexpr bool SPLIT = col_split<NY>();
   constexpr int NF = col_fft_len<NY>();
-  using C = ColCfg<NF>;
+  using C = ColPlanSel<NF, W>;
   using Plan = typename C::Plan;
   constexpr int T = C::T, E = NF / T;
   constexpr int R1 = Plan::radix[0], RL = Plan::radix[Plan::NPASS - 1];
@@ -679,30 +685,20 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
   constexpr int NT = T * W;
   __shared__ double red[(NT + 63) / 64];
 
-  const int inst = b / S.blocks_per_inst;
-  const int jb = b - inst * S.blocks_per_inst;
+  const int inst = b >> S.lg_blocks;
+  const int jb = b - (inst << S.lg_blocks);
   const int ntile = SPLIT ? S.blocks_per_inst / 2 : S.blocks_per_inst;
   const int part = SPLIT && jb >= ntile ? 1 : 0;
   const int tile = col_tile_of<W>(jb - part * ntile, ntile);
-  const Inst I = S.inst[inst];  // by value: the fields stay in registers
-  if (instance_stopped(I)) return;  // uniform over the workgroup
+  float2* const __restrict__ wf = S.W + (size_t)inst * S.field;
+  const Inst* const ip = S.inst + inst;
+  if (S.stopping && instance_stopped(ip)) return;  // uniform over the workgroup
   // frequency of position j, and the position of -ky within the half
   auto ky_of = [&](int j) { return SPLIT ? 2 * j + part : j; };
   auto mirror_pos = [&](int j) { return SPLIT && part ? NF - 1 - j : (NF - j) & (NF - 1); };
   // x-spectra in half form (col_op_half) use columns 0 .. nx/2 - 1 only
   constexpr bool HALF = col_op_half(OP);
-  const int nx = I.nx;
-  if constexpr (OP == COL_CHIRP1) {
-    // Stopping rule (Methods, "Reconstruction procedure"): |<x_k, x_k-1>| /
-    // (|x_k| |x_k-1|) above the threshold, from the FP64 partials of S0.
-    if (I.corr_partial && S.iter > 0 && tile == 0 && part == 0 && threadIdx.x == 0) {
-      double a[4] = {0.0, 0.0, 0.0, 0.0};
-      for (int i = 0; i < I.n_corr_partials; ++i)
-        for (int j = 0; j < 4; ++j) a[j] += I.corr_partial[4 * i + j];
-      const double c = sqrt(a[0] * a[0] + a[1] * a[1]) / sqrt(a[2] * a[3]);
-      if (c > S.corr_tol) *I.stop_iter = S.iter;
-    }
-  }
+  const int nx = S.nx;
   const int w = threadIdx.x % W, t = threadIdx.x / W;
   const int s = tile * W + w;
   // spectra: row part NF + j; W (split): stored row split_row(j, part), which
@@ -717,8 +713,28 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
   const auto tw = TS::forward(twl, S.tw_col);
   const auto twr = TS::inverse(twl, S.tw_col);
 
+  // Loads of W before the descriptor, as in the row sweeps.
   TwStage<TS::kLds, NT> tws;
   if constexpr (TS::kMode != 0) tws.load(TS::staged_from(S.tw_col, S.twn_col));
+  float2 v[E];
+  static_for<0, E / R1>([&](auto cc) {
+    static_for<0, R1>([&](auto qq) {
+      constexpr int c = decltype(cc)::value, q = decltype(qq)::value;
+      v[c * R1 + q] = gld(wf, o_w + (uint32_t)((T * c + q * M1) * WS * nx));
+    });
+  });
+  const Inst I = *ip;  // by value: the fields stay in registers
+  if constexpr (OP == COL_CHIRP1) {
+    // Stopping rule (Methods, "Reconstruction procedure"): |<x_k, x_k-1>| /
+    // (|x_k| |x_k-1|) above the threshold, from the FP64 partials of S0.
+    if (I.corr_partial && S.iter > 0 && tile == 0 && part == 0 && threadIdx.x == 0) {
+      double a[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int i = 0; i < I.n_corr_partials; ++i)
+        for (int j = 0; j < 4; ++j) a[j] += I.corr_partial[4 * i + j];
+      const double c = sqrt(a[0] * a[0] + a[1] * a[1]) / sqrt(a[2] * a[3]);
+      if (c > S.corr_tol) *I.stop_iter = S.iter;
+    }
+  }
   // The per-ky factor of the Fourier-domain step (chirp y factor; 1 - STF_y
   // in S11; IOTF_y in S5) staged in LDS like the twiddles, instead of one
   // global load per element (the 16-column chirp sweeps at 1024: 0.636 ->
@@ -733,36 +749,31 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
   if constexpr (YSTAGE) {
     static_for<0, KQ>([&](auto jj) {
       constexpr int k = decltype(jj)::value;
-      const int j = (int)threadIdx.x + k * NT;
-      // (half 1 uses positions below NF/2 only: its entry NF/2 would be ky = ny + 1)
-      if (j < NQ && !(part == 1 && j == NF / 2)) {
-        const uint32_t ky = (uint32_t)ky_of(j);
-        if constexpr (OP == COL_CHIRP1 || OP == COL_CHIRP1_CONJ) qys[k] = gld(I.qy1, ky);
-        else if constexpr (OP == COL_CHIRP2 || OP == COL_CHIRP2_CONJ) qys[k] = gld(I.qy2, ky);
-        else qys[k] = make_float2(gldf(OP == COL_NESTEROV ? I.gy : I.iy, ky), 0.f);
-      }
+      // (half 1 uses positions below NF/2 only: its entry NF/2 would be ky = ny + 1;
+      // clamped, not conditional, as in TwStage)
+      const int j = min((int)threadIdx.x + k * NT, NF / 2 - part);
+      const uint32_t ky = (uint32_t)ky_of(j);
+      if constexpr (OP == COL_CHIRP1 || OP == COL_CHIRP1_CONJ) qys[k] = gld(I.qy1, ky);
+      else if constexpr (OP == COL_CHIRP2 || OP == COL_CHIRP2_CONJ) qys[k] = gld(I.qy2, ky);
+      else qys[k] = make_float2(gldf(OP == COL_NESTEROV ? I.gy : I.iy, ky), 0.f);
     });
   }
   // staged factor of position j: that of min(j, mirror_pos(j))
   auto ytab = [&](int j) { return qyl[j <= NF / 2 - part ? j : mirror_pos(j)]; };
-  float2 v[E];
-  static_for<0, E / R1>([&](auto cc) {
-    static_for<0, R1>([&](auto qq) {
-      constexpr int c = decltype(cc)::value, q = decltype(qq)::value;
-      v[c * R1 + q] = gld(I.W, o_w + (uint32_t)((T * c + q * M1) * WS * nx));
-    });
-  });
   // Twiddles (and y factors) to LDS; the first pass needs none, and the
   // barrier after its LDS exchange orders these writes before the first use.
+  // The y factors, two round trips away, are written behind the first pass.
   if constexpr (TS::kMode != 0) tws.store(twl);
-  if constexpr (YSTAGE) {
-    static_for<0, KQ>([&](auto jj) {
-      constexpr int k = decltype(jj)::value;
-      const int j = (int)threadIdx.x + k * NT;
-      if (j < NQ && !(part == 1 && j == NF / 2)) qyl[j] = qys[k];
-    });
-  }
-  fft_forward<Plan, T>(v, t, tw, lv);
+  auto store_y = [&]() {
+    if constexpr (YSTAGE) {
+      static_for<0, KQ>([&](auto jj) {
+        constexpr int k = decltype(jj)::value;
+        const int j = (int)threadIdx.x + k * NT;
+        if (j < NQ && !(part == 1 && j == NF / 2)) qyl[j] = qys[k];
+      });
+    }
+  };
+  fft_forward<Plan, T>(v, t, tw, lv, store_y);
 
   // Fourier-domain step; element e = c*RL + r holds position j = t + T c + r ML.
   const int kx = HALF ? s : kx_of_col(s, nx);
@@ -959,7 +970,7 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
     static_for<0, E / R1>([&](auto cc) {
       static_for<0, R1>([&](auto qq) {
         constexpr int c = decltype(cc)::value, q = decltype(qq)::value;
-        gst(I.W, o_st + (uint32_t)((T * c + q * M1) * WS * nx), v[c * R1 + q]);
+        gst(wf, o_st + (uint32_t)((T * c + q * M1) * WS * nx), v[c * R1 + q]);
       });
     });
   }
@@ -977,8 +988,10 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
   }
 }
 
+template <int NY, int W> constexpr int col_threads() { return ColPlanSel<col_fft_len<NY>(), W>::T * W; }
+
 template <int NY, int W, int OP>
-__global__ void __launch_bounds__(ColSweepCfg<NY>::T * W, (col_min_waves<NY, W, OP>())) col_sweep(Sweep S) {
+__global__ void __launch_bounds__((col_threads<NY, W>()), (col_min_waves<NY, W, OP>())) col_sweep(Sweep S) {
   __shared__ float2 lds[ColLds<NY, W>::kExchange];
   __shared__ float2 twl[ColLds<NY, W>::kTwiddles];
   __shared__ float2 qyl[col_op_ystage(OP) ? ColLds<NY, W>::kYTable : 1];
@@ -1073,12 +1086,12 @@ hipError_t launch_row_one(int nblocks, const Sweep& S, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Row sweep `op` with radix plan `plan` (tunable sweeps only; the others
-// always run with their default plan).
+// Row sweep `op` with radix plan `plan` (tunable sweeps only; the others run
+// with their default plan, or the latency plan on the small sides).
 template <int N, int OP, bool PAIR>
 hipError_t launch_row_plan(int plan, int nblocks, const Sweep& S, hipStream_t st) {
   if (plan == 1) return launch_row_one<N, OP, 1, PAIR>(nblocks, S, st);
-  if constexpr (row_plan_count<N>() > 2) {
+  if constexpr (row_plan_count<N>() > 2 || (N <= 256 && !PAIR)) {
     if (plan == 2) return launch_row_one<N, OP, 2, PAIR>(nblocks, S, st);
   }
   if (plan == 0) return launch_row_one<N, OP, 0, PAIR>(nblocks, S, st);
@@ -1089,7 +1102,12 @@ template <int N, bool PAIR>
 hipError_t launch_row_np(int op, int plan, int nblocks, const Sweep& S, hipStream_t st) {
   switch (op) {
 #define PWF_TUNABLE(o) case o: return launch_row_plan<N, o, PAIR>(plan, nblocks, S, st);
-#define PWF_FIXED(o) case o: return launch_row_one<N, o, row_alt_default<N>(o) ? 1 : 0, PAIR>(nblocks, S, st);
+#define PWF_FIXED(o)                                                                                    \
+  case o:                                                                                               \
+    if constexpr (N <= 256 && !PAIR) {                                                                  \
+      if (plan == 2) return launch_row_one<N, o, 2, PAIR>(nblocks, S, st);                              \
+    }                                                                                                   \
+    return launch_row_one<N, o, row_alt_default<N>(o) ? 1 : 0, PAIR>(nblocks, S, st);
     PWF_TUNABLE(ROW_PSI_UPDATE) PWF_TUNABLE(ROW_PSI_UPDATE_CORR) PWF_TUNABLE(ROW_MUL_T) PWF_TUNABLE(ROW_MUL_CONJ_T) PWF_TUNABLE(ROW_INTENSITY)
     PWF_TUNABLE(ROW_BACKBLUR) PWF_TUNABLE(ROW_GRAD)
     PWF_FIXED(ROW_START) PWF_FIXED(ROW_FORWARD_OUT) PWF_FIXED(ROW_REAL_FFT) PWF_FIXED(ROW_CPLX_FFT)
@@ -1110,7 +1128,7 @@ hipError_t launch_row_n(int op, int plan, int nblocks, const Sweep& S, hipStream
 
 template <int N, int W>
 hipError_t launch_col_nw(int op, int nblocks, const Sweep& S, hipStream_t st) {
-  using C = ColSweepCfg<N>;
+  using C = ColPlanSel<col_fft_len<N>(), W>;
   const dim3 grid(nblocks), block(C::T * W);
   switch (op) {
 #define PWF_CASE(o) case o: hipLaunchKernelGGL((col_sweep<N, W, o>), grid, block, 0, st, S); break;
@@ -1128,6 +1146,9 @@ hipError_t launch_col_n(int width, int op, int nblocks, const Sweep& S, hipStrea
   using C = ColSweepCfg<N>;
   if (width == C::WA) return launch_col_nw<N, C::WA>(op, nblocks, S, st);
   if (width == C::WB) return launch_col_nw<N, C::WB>(op, nblocks, S, st);
+  if constexpr (N <= 256) {
+    if (width == kLatencyWidth) return launch_col_nw<N, kLatencyWidth>(op, nblocks, S, st);
+  }
   return hipErrorInvalidValue;
 }
 
