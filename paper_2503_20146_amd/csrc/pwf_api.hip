@@ -119,19 +119,6 @@ int row_plan(int n, int op) {
   return g_row_plan[i][op];
 }
 
-// Plan and tile width that a class of `count` instances runs with: what was set
-// (by the caller or the autotuner), else the latency plan where it applies,
-// else the built-in choice.
-int class_row_plan(int nx, int ny, int count, int op) {
-  if (op == pwf::ROW_PSI_UPDATE_CORR) op = pwf::ROW_PSI_UPDATE;
-  const bool set = pwf::row_plan_tunable(op) && g_row_plan[size_index(nx)][op] >= 0;
-  return !set && pwf::latency_shape(nx, ny, count) ? 2 : row_plan(nx, op);
-}
-int class_col_width(int nx, int ny, int count, int op) {
-  const bool set = g_col_width[size_index(ny)][op] != 0;
-  return !set && pwf::latency_shape(nx, ny, count) ? pwf::kLatencyWidth : col_width(ny, op);
-}
-
 // Row op of iteration sweep S0, S2, ..., S10 (-1 for other indices).
 int row_op_of_sweep(int sweep) {
   switch (sweep) {
@@ -313,12 +300,11 @@ int col_blocks(int nx, int ny, int op, int width) {
   return (pwf::col_op_half(op) ? nx / 2 : nx) / width * (pwf::col_split_n(ny) ? 2 : 1);
 }
 // loss partials: one per workgroup of the residual sweep
-int n_partials(int nx, int ny, int count) {
-  return col_blocks(nx, ny, pwf::COL_BLUR_LOSS, class_col_width(nx, ny, count, pwf::COL_BLUR_LOSS));
+int n_partials(const pwf_problem& p) {
+  return col_blocks(p.geom.nx, p.geom.ny, pwf::COL_BLUR_LOSS, col_width(p.geom.ny, pwf::COL_BLUR_LOSS));
 }
 // room for per-workgroup partials of a column sweep at the narrowest compiled tile
 int max_partials(const pwf_problem& p) {
-  // (the residual sweep's latency tiles, half as wide, cover half the columns)
   const int narrow = std::min(pwf::col_default_width(p.geom.ny), pwf::col_alt_width(p.geom.ny));
   return col_blocks(p.geom.nx, p.geom.ny, pwf::COL_CHIRP1, narrow);
 }
@@ -447,14 +433,13 @@ Layout make_loss_grad_layout(const pwf_problem* probs, int n) {
 
 // ------------------------------------------------------------------ descriptors
 
-// (count: instances of this grid shape in the batch)
-Inst base_inst(const pwf_problem& p, int count) {
+Inst base_inst(const pwf_problem& p) {
   Inst I;
   std::memset(&I, 0, sizeof(I));
   const pwf_geometry& g = p.geom;
   I.nx = g.nx;
   I.ny = g.ny;
-  I.n_partials = n_partials(g.nx, g.ny, count);
+  I.n_partials = n_partials(p);
   I.t = (const float2*)p.diffuser;
   const double p2 = g.pixel_m * g.pixel_m;
   I.chirp1_rev = g.z1_m * g.wavelength_m / (2.0 * p2);
@@ -523,11 +508,6 @@ struct Class {
 struct Batch {
   std::vector<int> order;  // descriptor slot -> caller index
   std::vector<Class> classes;
-  int count(const pwf_problem& p) const {   // instances of p's grid shape
-    for (const Class& c : classes)
-      if (c.nx == p.geom.nx && c.ny == p.geom.ny) return c.count;
-    return 0;
-  }
 };
 
 Batch group(const pwf_problem* probs, int n) {
@@ -565,8 +545,16 @@ struct Launcher {
   hipStream_t st;
   double corr_tol = 0.0;
   bool merged = false;   // batch_merged(B): one launch per sweep over the classes
-  int width_of(const Class& c, int op) const { return class_col_width(c.nx, c.ny, c.count, op); }
-  int plan_of(const Class& c, int op) const { return class_row_plan(c.nx, c.ny, c.count, op); }
+  bool latency = false;  // the latency plans, where nothing is set (forward calls)
+  int width_of(const Class& c, int op) const {
+    const bool set = g_col_width[size_index(c.ny)][op] != 0;
+    return latency && !set && pwf::latency_shape(c.nx, c.ny, c.count) ? pwf::kLatencyWidth : col_width(c.ny, op);
+  }
+  int plan_of(const Class& c, int op) const {
+    if (op == pwf::ROW_PSI_UPDATE_CORR) op = pwf::ROW_PSI_UPDATE;
+    const bool set = pwf::row_plan_tunable(op) && g_row_plan[size_index(c.nx)][op] >= 0;
+    return latency && !set && pwf::latency_shape(c.nx, c.ny, c.count) ? 2 : row_plan(c.nx, op);
+  }
   Inst* dev_desc() const { return (Inst*)(ws + L.desc); }
   int32_t* status() const { return (int32_t*)(ws + L.status); }
 
@@ -779,7 +767,7 @@ pwf_status forward_impl(const pwf_problem* problems, int32_t n, const void* cons
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.psi_src = (const float2*)psi[i];
@@ -792,7 +780,8 @@ pwf_status forward_impl(const pwf_problem* problems, int32_t n, const void* cons
   }
   PWF_TRY(upload(*ctx, desc.data(), sizeof(Inst) * n, ws + L.desc, st));
   PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
-  const Launcher K{*ctx, ws, L, B, st};
+  Launcher K{*ctx, ws, L, B, st};
+  K.latency = true;
   PWF_TRY(K.row(pwf::ROW_START));
   PWF_TRY(K.col(pwf::COL_CHIRP1));
   PWF_TRY(K.row(pwf::ROW_MUL_T));
@@ -820,7 +809,7 @@ void loss_grad_descriptors(const pwf_problem* problems, int32_t n, const Batch& 
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -894,7 +883,7 @@ pwf_status pwf_gradient(const pwf_problem* problems, int32_t n, const void* cons
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -980,7 +969,7 @@ pwf_status pwf_state_init(const pwf_problem* problems, int32_t n, pwf_state* sta
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.y = y[i];
@@ -1022,7 +1011,7 @@ pwf_status pwf_step(const pwf_problem* problems, int32_t n, pwf_state* states, d
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.k0 = states[i].k;
     I.W = (float2*)(ws + L.W[i]);
@@ -1075,7 +1064,7 @@ struct JointCfg {
 pwf_status joint_step(const Launcher& K, const pwf_problem* probs, int n, const JointCfg& jc) {
   const pwf_problem& p = probs[0];
   const size_t m = (size_t)p.geom.nx * p.geom.ny;
-  const int count = p.geom.ny / pwf::row_rows_per_block(p.geom.nx, class_row_plan(p.geom.nx, p.geom.ny, n, pwf::ROW_MUL_T));
+  const int count = p.geom.ny / pwf::row_rows_per_block(p.geom.nx, row_plan(p.geom.nx, pwf::ROW_MUL_T));
   float2* t = (float2*)p.diffuser;
   PWF_HIP(pwf::launch_joint_update((float*)(K.ws + K.L.u1max), n, count, (size_t)p.geom.ny,
                                    (const float2*)(K.ws + K.L.u1[0]), field_bytes(p) / sizeof(float2), m, t,
@@ -1188,7 +1177,7 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -1208,8 +1197,7 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
       I.corr_partial = (double*)(ws + L.corr[i]);
       I.n_corr_partials = problems[i].geom.ny /
                           pwf::row_rows_per_block(problems[i].geom.nx,
-                                                  class_row_plan(problems[i].geom.nx, problems[i].geom.ny,
-                                                                 B.count(problems[i]), pwf::ROW_PSI_UPDATE));
+                                                  row_plan(problems[i].geom.nx, pwf::ROW_PSI_UPDATE));
       I.stop_iter = (int32_t*)(ws + L.stop) + i;
     }
   }
@@ -1353,7 +1341,7 @@ pwf_status pwf_bench_sweep(const pwf_problem* problems, int32_t n, int32_t sweep
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -1445,7 +1433,7 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -1471,13 +1459,6 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
     one.classes = {c};
     const Launcher K{*ctx, ws, L, one, st};
     const int cidx = size_index(c.ny), ridx = size_index(c.nx);
-    if (pwf::latency_shape(c.nx, c.ny, c.count)) {   // the latency plan, where nothing is set
-      for (int sweep = 0; sweep < 12; ++sweep) {
-        if (sweep & 1) g_col_width[cidx][col_op_of_sweep(sweep)] = 0;
-        else g_row_plan[ridx][row_op_of_sweep(sweep)] = -1;
-      }
-      continue;
-    }
     // time `reps` launches of one sweep (after a warm-up launch)
     auto timed = [&](auto launch, float* ms) -> pwf_status {
       PWF_TRY(launch());
@@ -1576,10 +1557,9 @@ std::vector<int> batch_sides(const Batch& B) {
 
 std::string tuning_line(const std::string& arch, const std::string& mix, int side) {
   std::string l = arch + ' ' + mix + ' ' + std::to_string(side) + " c";
-  // (0 and -1: the built-in choice)
-  for (int sw = 1; sw < 12; sw += 2) l += ' ' + std::to_string(g_col_width[size_index(side)][col_op_of_sweep(sw)]);
+  for (int sw = 1; sw < 12; sw += 2) l += ' ' + std::to_string(col_width(side, col_op_of_sweep(sw)));
   l += " r";
-  for (int sw = 0; sw < 12; sw += 2) l += ' ' + std::to_string(g_row_plan[size_index(side)][row_op_of_sweep(sw)]);
+  for (int sw = 0; sw < 12; sw += 2) l += ' ' + std::to_string(row_plan(side, row_op_of_sweep(sw)));
   return l;
 }
 
@@ -1598,8 +1578,7 @@ int apply_tuning_line(const std::string& line, const std::string& arch, const st
   const int i = size_index(side);
   if (i < 0) return 0;
   for (int k = 0; k < 6; ++k) {
-    if ((w[k] != 0 && !pwf::col_width_supported(side, w[k])) || pl[k] < -1 || pl[k] >= pwf::row_plan_count_n(side))
-      return 0;
+    if (!pwf::col_width_supported(side, w[k]) || pl[k] < 0 || pl[k] >= pwf::row_plan_count_n(side)) return 0;
   }
   for (int k = 0; k < 6; ++k) {
     g_col_width[i][col_op_of_sweep(2 * k + 1)] = w[k];
@@ -1688,7 +1667,7 @@ pwf_status pwf_solve_plain(const pwf_problem* problem, const float* y, void* psi
   const pwf_problem& p = *problem;
   const int nx = p.geom.nx, ny = p.geom.ny;
   const size_t m = (size_t)nx * ny;
-  Inst I = base_inst(p, 1);
+  Inst I = base_inst(p);
   attach_tables(I, ws, L, 0);
   I.y = y;
   I.maxt2 = (const float*)(ws + L.maxt2);
@@ -1820,7 +1799,7 @@ pwf_status pwf_diffuser_from_reference(const pwf_problem* problem, const float* 
   PWF_TRY(context_for_current(&ctx));
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  Inst I = base_inst(*problem, 1);
+  Inst I = base_inst(*problem);
   attach_tables(I, ws, L, 0);
   I.W = (float2*)(ws + L.W[0]);
   I.y = ref;

@@ -182,7 +182,7 @@ template <> struct RowCfgAlt<1024> { using Plan = FftPlan<1024, 16, 16, 4>; stat
 template <> struct RowCfgAlt<2048> { using Plan = FftPlan<2048, 16, 16, 8>; static constexpr int T = 128, RW = 2; };
 // A third plan on the large sides: the alternative plan's radices in the other
 // order (small radix first), searched by the autotuner.
-// On the small sides it is the plan of latency-bound batches (latency_shape).
+// On the small sides it is the plan of latency-bound forward calls (latency_shape).
 template <int N> struct RowCfgAlt2 : RowCfg<N> {};
 template <> struct RowCfgAlt2<128>  { using Plan = FftPlan<128, 4, 4, 4, 2>;  static constexpr int T = 32,  RW = 8; };
 template <> struct RowCfgAlt2<256>  { using Plan = FftPlan<256, 4, 4, 4, 4>;  static constexpr int T = 64,  RW = 4; };
@@ -207,21 +207,24 @@ template <> struct ColCfg<1024> { using Plan = FftPlan<1024, 16, 16, 4>; static 
 template <> struct ColCfg<2048> { using Plan = FftPlan<2048, 16, 16, 8>; static constexpr int T = 128, WA = 4,  WB = 8; };
 
 // Column configuration by tile width: 8-column tiles of 128- and 256-point
-// columns are those of latency-bound batches, with the row plans' four elements
-// per lane.
+// columns are those of latency-bound forward calls, with the row plans' four
+// elements per lane.
 constexpr int kLatencyWidth = 8;
 template <int N, int W> struct ColPlanSel : ColCfg<N> {};
 template <> struct ColPlanSel<128, kLatencyWidth> { using Plan = FftPlan<128, 4, 4, 4, 2>; static constexpr int T = 32; };
 template <> struct ColPlanSel<256, kLatencyWidth> { using Plan = FftPlan<256, 4, 4, 4, 4>; static constexpr int T = 64; };
 
-// Batches that do not fill the chip on small grids: a wave's own chain of
-// arithmetic and LDS exchanges is then the time of a sweep, not the memory.
-// At 16 elements per lane a 128^2 field is 16 waves of ~1500 operations each;
-// four elements per lane make it 64 waves of a third of that, for two more LDS
-// exchanges: 82 -> 58 us an iteration for one field of 128^2, 109 -> 96 for 64
-// (row sweeps alone), while 256 of them, bound by memory, ran 2% slower.
-// Both sides are at most 256: on larger grids the preconditioner amplifies the
-// rounding differences between the plans, and fields fill more of the chip.
+// Forward calls on batches of small grids that do not fill the chip: a wave's
+// own chain of arithmetic and LDS exchanges is then the time of a sweep, not the
+// memory.  At 16 elements per lane a 128^2 field is 16 waves of ~1500 operations
+// each; four elements per lane make it 64 waves of a third of that, for two more
+// LDS exchanges: 50.5 -> 42.7 us for pwf_forward of one 256^2 field; 64 fields of
+// 128^2 still gained (109 -> 96 us for twelve sweeps), 256 of them, bound by
+// memory, ran 2% slower.  The forward's result has the error of the built-in
+// plans (1.5e-7 of its norm).  The solves, gradients and steps stay on the
+// built-in plans, although one field of 128^2 ran its iterations 1.4 times as
+// fast: their results amplify the order of rounding, and those of a user's small
+// reconstructions would no longer be the same bits.
 constexpr int kLatencyPixels = 1 << 20;
 constexpr bool latency_shape(int nx, int ny, int count) {
   return nx <= 256 && ny <= 256 && (long long)nx * ny * count <= kLatencyPixels;

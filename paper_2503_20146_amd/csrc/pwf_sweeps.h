@@ -1087,11 +1087,12 @@ hipError_t launch_row_one(int nblocks, const Sweep& S, hipStream_t st) {
 }
 
 // Row sweep `op` with radix plan `plan` (tunable sweeps only; the others run
-// with their default plan, or the latency plan on the small sides).
+// with their default plan, and those of the forward model on the small sides
+// also with the latency plan).
 template <int N, int OP, bool PAIR>
 hipError_t launch_row_plan(int plan, int nblocks, const Sweep& S, hipStream_t st) {
   if (plan == 1) return launch_row_one<N, OP, 1, PAIR>(nblocks, S, st);
-  if constexpr (row_plan_count<N>() > 2 || (N <= 256 && !PAIR)) {
+  if constexpr (row_plan_count<N>() > 2 || (N <= 256 && !PAIR && row_op_forward(OP))) {
     if (plan == 2) return launch_row_one<N, OP, 2, PAIR>(nblocks, S, st);
   }
   if (plan == 0) return launch_row_one<N, OP, 0, PAIR>(nblocks, S, st);
@@ -1104,7 +1105,7 @@ hipError_t launch_row_np(int op, int plan, int nblocks, const Sweep& S, hipStrea
 #define PWF_TUNABLE(o) case o: return launch_row_plan<N, o, PAIR>(plan, nblocks, S, st);
 #define PWF_FIXED(o)                                                                                    \
   case o:                                                                                               \
-    if constexpr (N <= 256 && !PAIR) {                                                                  \
+    if constexpr (N <= 256 && !PAIR && row_op_forward(o)) {                                             \
       if (plan == 2) return launch_row_one<N, o, 2, PAIR>(nblocks, S, st);                              \
     }                                                                                                   \
     return launch_row_one<N, o, row_alt_default<N>(o) ? 1 : 0, PAIR>(nblocks, S, st);
@@ -1124,6 +1125,20 @@ template <int N>
 hipError_t launch_row_n(int op, int plan, int nblocks, const Sweep& S, hipStream_t st) {
   return S.pair_half > 0 ? launch_row_np<N, true>(op, plan, nblocks, S, st)
                          : launch_row_np<N, false>(op, plan, nblocks, S, st);
+}
+
+// Column sweep `op` of the forward model on the latency plan (side <= 256).
+template <int N>
+hipError_t launch_col_latency(int op, int nblocks, const Sweep& S, hipStream_t st) {
+  constexpr int W = kLatencyWidth;
+  const dim3 grid(nblocks), block(col_threads<N, W>());
+  switch (op) {
+#define PWF_CASE(o) case o: hipLaunchKernelGGL((col_sweep<N, W, o>), grid, block, 0, st, S); break;
+    PWF_CASE(COL_CHIRP1) PWF_CASE(COL_CHIRP2) PWF_CASE(COL_BLUR)
+#undef PWF_CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 template <int N, int W>
@@ -1147,7 +1162,7 @@ hipError_t launch_col_n(int width, int op, int nblocks, const Sweep& S, hipStrea
   if (width == C::WA) return launch_col_nw<N, C::WA>(op, nblocks, S, st);
   if (width == C::WB) return launch_col_nw<N, C::WB>(op, nblocks, S, st);
   if constexpr (N <= 256) {
-    if (width == kLatencyWidth) return launch_col_nw<N, kLatencyWidth>(op, nblocks, S, st);
+    if (width == kLatencyWidth) return launch_col_latency<N>(op, nblocks, S, st);
   }
   return hipErrorInvalidValue;
 }
