@@ -313,7 +313,7 @@ size_t table_bytes(const pwf_problem& p) {
 }
 
 struct Layout {
-  size_t status = 0, maxt2 = 0, maxt2_part = 0, desc = 0, partials = 0;
+  size_t status = 0, maxt2 = 0, desc = 0, partials = 0;
   std::vector<size_t> W, psi_hat, z_hat, v, psi, y_hat, extra0, extra1, part, tables, corr;
   std::vector<size_t> u1;            // joint diffuser mode only
   size_t u1max = 0, dsum = 0;        // joint diffuser mode only
@@ -341,8 +341,6 @@ Layout make_layout(const pwf_problem* probs, int n, bool joint = false) {
   off += kAlign;
   L.maxt2 = off;
   off += align_up(sizeof(float) * n);
-  L.maxt2_part = off;
-  off += align_up(sizeof(float) * (size_t)pwf::maxabs2_blocks() * n);
   L.desc = off;
   off += align_up(sizeof(Inst) * n);
   L.part.resize(n);
@@ -667,40 +665,67 @@ pwf_status check_ws(const pwf_problem* probs, int n, void* ws, size_t ws_bytes, 
   return PWF_OK;
 }
 
-// max|t|^2 for every distinct diffuser; sets inst.maxt2.
-// (the distinct diffusers in launches of up to kMaxabs2Batch: a batch of
-// distinct ROIs would otherwise queue two small launches per instance)
-pwf_status launch_maxt2(const pwf_problem* probs, int n, const Batch& B, std::vector<Inst>& desc, char* ws,
-                        const Layout& L, hipStream_t st) {
+// Slot of every instance's max|t|^2 (one per distinct diffuser): sets inst.maxt2.
+void assign_maxt2(const pwf_problem* probs, int n, const Batch& B, std::vector<Inst>& desc, char* ws, const Layout& L) {
   std::vector<const void*> seen;
-  pwf::Maxabs2Batch mb;
-  std::memset(&mb, 0, sizeof(mb));
-  int first = 0;  // slot of mb's first entry
-  auto flush = [&]() -> pwf_status {
-    if (mb.n == 0) return PWF_OK;
-    float* part = (float*)(ws + L.maxt2_part) + (size_t)first * pwf::maxabs2_blocks();
-    PWF_HIP(pwf::launch_maxabs2_batch(mb, part, st));
-    first += mb.n;
-    mb.n = 0;
-    return PWF_OK;
-  };
   for (int s = 0; s < n; ++s) {
     const pwf_problem& p = probs[B.order[s]];
-    int slot = -1;
-    for (size_t j = 0; j < seen.size(); ++j)
-      if (seen[j] == p.diffuser) slot = (int)j;
-    if (slot < 0) {
-      slot = (int)seen.size();
-      seen.push_back(p.diffuser);
-      if (mb.n == pwf::kMaxabs2Batch) PWF_TRY(flush());
-      mb.t[mb.n] = (const float2*)p.diffuser;
-      mb.m[mb.n] = (size_t)p.geom.nx * p.geom.ny;
-      mb.out[mb.n] = (float*)(ws + L.maxt2) + slot;
-      ++mb.n;
-    }
+    size_t slot = std::find(seen.begin(), seen.end(), p.diffuser) - seen.begin();
+    if (slot == seen.size()) seen.push_back(p.diffuser);
     desc[s].maxt2 = (const float*)(ws + L.maxt2) + slot;
   }
-  return flush();
+}
+
+// max|t|^2 of every distinct diffuser, in launches of up to kMaxabs2Batch, into
+// the slots of assign_maxt2, which setup() has cleared.
+pwf_status launch_maxt2(const pwf_problem* probs, int n, const Batch& B, const std::vector<Inst>& desc,
+                        hipStream_t st) {
+  std::vector<const float*> seen;
+  pwf::Maxabs2Batch mb;
+  mb.n = 0;
+  for (int s = 0; s < n; ++s) {
+    if (std::find(seen.begin(), seen.end(), desc[s].maxt2) != seen.end()) continue;
+    seen.push_back(desc[s].maxt2);
+    const pwf_problem& p = probs[B.order[s]];
+    if (mb.n == pwf::kMaxabs2Batch) {
+      PWF_HIP(pwf::launch_maxabs2(mb, st));
+      mb.n = 0;
+    }
+    mb.t[mb.n] = (const float2*)p.diffuser;
+    mb.m[mb.n] = (size_t)p.geom.nx * p.geom.ny;
+    mb.out[mb.n] = (float*)desc[s].maxt2;
+    ++mb.n;
+  }
+  if (mb.n) PWF_HIP(pwf::launch_maxabs2(mb, st));
+  return PWF_OK;
+}
+
+// Set-up of a call: descriptors to the workspace, window tables, and, for calls
+// that compute a loss (`clear`), the status flag and the slots of max|t|^2 (in
+// front of the descriptors) cleared.  Up to kSetupLaunches x kSetupInsts
+// instances travel as kernel arguments (about 4 us a launch); a larger batch
+// through the pinned staging buffer, whose copy starts the first sweep some
+// 25 us later, small against the sweeps of such a batch.
+constexpr int kSetupLaunches = 4;
+constexpr int kSetupByArgs = kSetupLaunches * pwf::kSetupInsts;
+pwf_status setup(Context& c, char* ws, const Layout& L, const Inst* desc, int n, bool clear, hipStream_t st) {
+  if (n <= kSetupByArgs) {
+    pwf::SetupArgs A;
+    A.words = (uint32_t*)(ws + L.status);
+    A.clear = clear ? (int32_t)((L.desc - L.status) / 4) : 0;
+    for (int s = 0; s < n; s += pwf::kSetupInsts) {
+      const int m = std::min(n - s, pwf::kSetupInsts);
+      std::memcpy(A.inst, desc + s, sizeof(Inst) * m);
+      A.dst = (Inst*)(ws + L.desc) + s;
+      PWF_HIP(pwf::launch_setup(A, m, st));
+      A.clear = 0;
+    }
+    return PWF_OK;
+  }
+  if (clear) PWF_HIP(pwf::launch_fill_zero(ws + L.status, L.desc - L.status, st));
+  PWF_TRY(upload(c, desc, sizeof(Inst) * n, ws + L.desc, st));
+  PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
+  return PWF_OK;
 }
 
 }  // namespace
@@ -778,8 +803,7 @@ pwf_status forward_impl(const pwf_problem* problems, int32_t n, const void* cons
       I.rmse_scale = (float)(100.0 / ref_mean[i]);
     }
   }
-  PWF_TRY(upload(*ctx, desc.data(), sizeof(Inst) * n, ws + L.desc, st));
-  PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
+  PWF_TRY(setup(*ctx, ws, L, desc.data(), n, false, st));
   Launcher K{*ctx, ws, L, B, st};
   K.latency = true;
   PWF_TRY(K.row(pwf::ROW_START));
@@ -825,10 +849,9 @@ void loss_grad_descriptors(const pwf_problem* problems, int32_t n, const Batch& 
   }
 }
 
-// After the descriptors are in place: window tables, spectrum of y, forward
-// model, loss and the back-propagated gradient.
-pwf_status loss_grad_sequence(const Launcher& K, int32_t n) {
-  PWF_HIP(pwf::launch_build_tables((const Inst*)(K.ws + K.L.desc), n, K.st));
+// After the set-up: spectrum of y, forward model, loss and the back-propagated
+// gradient.
+pwf_status loss_grad_sequence(const Launcher& K) {
   PWF_TRY(K.row(pwf::ROW_REAL_FFT));
   PWF_TRY(K.col(pwf::COL_SPEC_YHAT));
   PWF_TRY(K.row(pwf::ROW_START));
@@ -897,10 +920,9 @@ pwf_status pwf_gradient(const pwf_problem* problems, int32_t n, const void* cons
     I.loss_partial = (double*)(ws + L.part[i]);
     I.loss_dst = loss_out ? loss_out + i : nullptr;
   }
-  PWF_HIP(pwf::launch_fill_zero(ws + L.status, 16, st));
-  PWF_TRY(launch_maxt2(problems, n, B, desc, ws, L, st));
-  PWF_TRY(upload(*ctx, desc.data(), sizeof(Inst) * n, ws + L.desc, st));
-  PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
+  assign_maxt2(problems, n, B, desc, ws, L);
+  PWF_TRY(setup(*ctx, ws, L, desc.data(), n, true, st));
+  if (want_g || want_d) PWF_TRY(launch_maxt2(problems, n, B, desc, st));
   const Launcher K{*ctx, ws, L, B, st};
   if (want_d) {
     // spectrum of psi for the regulariser (I.psi is null: nothing is copied)
@@ -946,9 +968,8 @@ pwf_status pwf_loss_grad(const pwf_problem* problems, int32_t n, const void* con
   const Batch B = group(problems, n);
   std::vector<Inst> desc(n);
   loss_grad_descriptors(problems, n, B, psi, y, grad_out, loss_out, ws, L, desc.data());
-  PWF_HIP(pwf::launch_fill_zero(ws + L.status, 16, st));
-  PWF_TRY(upload(*ctx, desc.data(), sizeof(Inst) * n, ws + L.desc, st));
-  return loss_grad_sequence(Launcher{*ctx, ws, L, B, st}, n);
+  PWF_TRY(setup(*ctx, ws, L, desc.data(), n, true, st));
+  return loss_grad_sequence(Launcher{*ctx, ws, L, B, st});
 }
 
 pwf_status pwf_state_init(const pwf_problem* problems, int32_t n, pwf_state* states, const void* const* psi0,
@@ -980,8 +1001,7 @@ pwf_status pwf_state_init(const pwf_problem* problems, int32_t n, pwf_state* sta
     I.z_hat = (float2*)states[i].z_hat;
     I.loss_partial = (double*)(ws + L.part[i]);
   }
-  PWF_TRY(upload(*ctx, desc.data(), sizeof(Inst) * n, ws + L.desc, st));
-  PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
+  PWF_TRY(setup(*ctx, ws, L, desc.data(), n, false, st));
   const Launcher K{*ctx, ws, L, B, st};
   PWF_TRY(K.row(pwf::ROW_REAL_FFT));
   PWF_TRY(K.col(pwf::COL_SPEC_YHAT));
@@ -1025,10 +1045,9 @@ pwf_status pwf_step(const pwf_problem* problems, int32_t n, pwf_state* states, d
     I.loss_partial = (double*)(ws + L.part[i]);
     I.loss_dst = loss_out ? loss_out + i : nullptr;
   }
-  PWF_HIP(pwf::launch_fill_zero(ws + L.status, 16, st));
-  PWF_TRY(launch_maxt2(problems, n, B, desc, ws, L, st));
-  PWF_TRY(upload(*ctx, desc.data(), sizeof(Inst) * n, ws + L.desc, st));
-  PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
+  assign_maxt2(problems, n, B, desc, ws, L);
+  PWF_TRY(setup(*ctx, ws, L, desc.data(), n, true, st));
+  PWF_TRY(launch_maxt2(problems, n, B, desc, st));
   const Launcher K{*ctx, ws, L, B, st};
   PWF_TRY(K.row(pwf::ROW_START));
   PWF_TRY(K.col(pwf::COL_CHIRP1));
@@ -1051,8 +1070,6 @@ pwf_status pwf_step(const pwf_problem* problems, int32_t n, pwf_state* states, d
 
 namespace {
 
-// The solve sequence after the descriptor upload: setup, iters x 12 sweeps,
-// final inverse pass into psi_out.
 // Joint diffuser refinement (Results, "Diffuser transmission function"):
 // after every iteration, t <- t - eta_t sum_j conj(u1_j) a2_j / sum_j max|u1_j|^2
 // over all instances (which share t), then max|t|^2 for the next gradient.
@@ -1068,19 +1085,15 @@ pwf_status joint_step(const Launcher& K, const pwf_problem* probs, int n, const 
   float2* t = (float2*)p.diffuser;
   PWF_HIP(pwf::launch_joint_update((float*)(K.ws + K.L.u1max), n, count, (size_t)p.geom.ny,
                                    (const float2*)(K.ws + K.L.u1[0]), field_bytes(p) / sizeof(float2), m, t,
-                                   jc.eta_t, (double*)(K.ws + K.L.dsum), K.st));
-  PWF_HIP(pwf::launch_maxabs2(t, m, (float*)(K.ws + K.L.maxt2_part), (float*)(K.ws + K.L.maxt2), K.st));
+                                   jc.eta_t, (double*)(K.ws + K.L.dsum), (float*)(K.ws + K.L.maxt2), K.st));
   return PWF_OK;
 }
 
-pwf_status solve_sequence(const Launcher& K, const pwf_problem* probs, int n, std::vector<Inst>& desc, int iters,
-                          const JointCfg& jc) {
-  (void)desc;
-  // spectrum of y (uses W as scratch), then clear the status word and W,
-  // psi_hat, z_hat of every instance (contiguous regions): psi = z = 0
+pwf_status solve_sequence(const Launcher& K, const pwf_problem* probs, int n, int iters, const JointCfg& jc) {
+  // spectrum of y (uses W as scratch), then clear W, psi_hat, z_hat of every
+  // instance (contiguous regions): psi = z = 0
   PWF_TRY(K.row(pwf::ROW_REAL_FFT));
   PWF_TRY(K.col(pwf::COL_SPEC_YHAT));
-  PWF_HIP(pwf::launch_fill_zero(K.ws + K.L.status, 16, K.st));
   PWF_HIP(pwf::launch_fill_zero(K.ws + K.L.W[K.B.order[0]], K.L.v[K.B.order[0]] - K.L.W[K.B.order[0]], K.st));
   const int s0 = K.corr_tol > 0.0 ? pwf::ROW_PSI_UPDATE_CORR : pwf::ROW_PSI_UPDATE;
   auto iterate = [&](const Launcher& Q) -> pwf_status {
@@ -1201,23 +1214,8 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
       I.stop_iter = (int32_t*)(ws + L.stop) + i;
     }
   }
-  // maxt2 slots depend only on the diffuser pointers; fill desc before upload
-  {
-    std::vector<const void*> seen;
-    for (int s = 0; s < n; ++s) {
-      const pwf_problem& p = problems[B.order[s]];
-      int slot = -1;
-      for (size_t j = 0; j < seen.size(); ++j)
-        if (seen[j] == p.diffuser) slot = (int)j;
-      if (slot < 0) {
-        slot = (int)seen.size();
-        seen.push_back(p.diffuser);
-      }
-      desc[s].maxt2 = (const float*)(ws + L.maxt2) + slot;
-    }
-  }
-  PWF_TRY(upload(*ctx, desc.data(), sizeof(Inst) * n, ws + L.desc, st));
-  PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
+  assign_maxt2(problems, n, B, desc, ws, L);
+  PWF_TRY(setup(*ctx, ws, L, desc.data(), n, true, st));
   if (iters_done)
     for (int i = 0; i < n; ++i) iters_done[i] = iters;
 
@@ -1226,9 +1224,8 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
     K.corr_tol = corr_tol;
     K.merged = merged;
     if (corr_mode) PWF_HIP(pwf::launch_fill_zero(ws + L.stop, align_up(sizeof(int32_t) * n), s));
-    std::vector<Inst> tmp = desc;
-    PWF_TRY(launch_maxt2(problems, n, B, tmp, ws, L, s));
-    return solve_sequence(K, problems, n, desc, iters, jc);
+    PWF_TRY(launch_maxt2(problems, n, B, desc, s));
+    return solve_sequence(K, problems, n, iters, jc);
   };
 
   auto report = [&]() -> pwf_status {
@@ -1337,7 +1334,6 @@ pwf_status pwf_bench_sweep(const pwf_problem* problems, int32_t n, int32_t sweep
   char* ws = (char*)workspace;
   const Batch B = group(problems, n);
   std::vector<Inst> desc(n);
-  std::vector<const void*> seen;
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
@@ -1350,17 +1346,9 @@ pwf_status pwf_bench_sweep(const pwf_problem* problems, int32_t n, int32_t sweep
     I.z_hat = (float2*)(ws + L.z_hat[i]);
     I.y_hat = (float2*)(ws + L.y_hat[i]);
     I.loss_partial = (double*)(ws + L.part[i]);
-    int slot = -1;
-    for (size_t j = 0; j < seen.size(); ++j)
-      if (seen[j] == problems[i].diffuser) slot = (int)j;
-    if (slot < 0) {
-      slot = (int)seen.size();
-      seen.push_back(problems[i].diffuser);
-    }
-    I.maxt2 = (const float*)(ws + L.maxt2) + slot;
   }
-  PWF_TRY(upload(*ctx, desc.data(), sizeof(Inst) * n, ws + L.desc, st));
-  PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
+  assign_maxt2(problems, n, B, desc, ws, L);
+  PWF_TRY(setup(*ctx, ws, L, desc.data(), n, false, st));
   const Launcher K{*ctx, ws, L, B, st};
   static const int kOps[12][2] = {
       {0, pwf::ROW_PSI_UPDATE}, {1, pwf::COL_CHIRP1},      {0, pwf::ROW_MUL_T},      {1, pwf::COL_CHIRP2},
@@ -1444,8 +1432,7 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
     I.loss_partial = (double*)(ws + L.part[i]);
     I.maxt2 = (const float*)(ws + L.maxt2);
   }
-  PWF_TRY(upload(*ctx, desc.data(), sizeof(Inst) * n, ws + L.desc, st));
-  PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
+  PWF_TRY(setup(*ctx, ws, L, desc.data(), n, false, st));
   // every field region (timing does not depend on the values)
   PWF_HIP(pwf::launch_fill_zero(ws + L.W[B.order[0]], L.extra0[0] - L.W[B.order[0]], st));
   hipEvent_t e0, e1;
@@ -1672,8 +1659,7 @@ pwf_status pwf_solve_plain(const pwf_problem* problem, const float* y, void* psi
   I.y = y;
   I.maxt2 = (const float*)(ws + L.maxt2);
   Inst* dI = (Inst*)(ws + L.desc);
-  PWF_TRY(upload(*ctx, &I, sizeof(Inst), dI, st));
-  PWF_HIP(pwf::launch_build_tables(dI, 1, st));
+  PWF_TRY(setup(*ctx, ws, L, &I, 1, true, st));
   float2* psi = (float2*)psi_out;
   float2* Z = (float2*)(ws + L.W[0]);
   float2* X = (float2*)(ws + L.psi_hat[0]);
@@ -1687,8 +1673,7 @@ pwf_status pwf_solve_plain(const pwf_problem* problem, const float* y, void* psi
   const float2* twx = ctx->tw[size_index(nx)];
   const float2* twy = ctx->twc[size_index(ny)];
 
-  PWF_HIP(pwf::launch_fill_zero(status, 16, st));
-  PWF_HIP(pwf::launch_maxabs2((const float2*)p.diffuser, m, (float*)(ws + L.maxt2_part), (float*)(ws + L.maxt2), st));
+  PWF_TRY(launch_maxt2(problem, 1, group(problem, 1), {I}, st));
   PWF_HIP(pwf::launch_fill_zero(psi, m * sizeof(float2), st));
   PWF_HIP(pwf::launch_fill_zero(Z, m * sizeof(float2), st));
 
@@ -1806,8 +1791,7 @@ pwf_status pwf_diffuser_from_reference(const pwf_problem* problem, const float* 
   I.out = (float2*)t_out;
   I.wiener_eps = (float)eps;
   Inst* dI = (Inst*)(ws + L.desc);
-  PWF_TRY(upload(*ctx, &I, sizeof(Inst), dI, st));
-  PWF_HIP(pwf::launch_build_tables(dI, 1, st));
+  PWF_TRY(setup(*ctx, ws, L, &I, 1, false, st));
   // Results, "Diffuser transmission function": Wiener deconvolution by the
   // IOTF, zero-phase square root, back-propagation over L2, as five sweeps
   // (one kernel per operation was twelve launches)
@@ -2194,13 +2178,20 @@ pwf_status pwf_loss_grad_noalloc(const pwf_problem* problems, int32_t n, const v
   hipStream_t st = (hipStream_t)stream;
   char* ws = d->base + kScratchTableBytes;
   const Batch B = group(problems, n);
+  if (n <= kSetupByArgs) {   // as kernel arguments: nothing on the host outlives the call
+    Inst desc[kSetupByArgs];
+    loss_grad_descriptors(problems, n, B, psi, y, grad_out, loss_out, ws, L, desc);
+    PWF_TRY(setup(d->tables, ws, L, desc, n, true, st));
+    return loss_grad_sequence(Launcher{d->tables, ws, L, B, st});
+  }
   // the previous call's copy must have read host_desc before it is rewritten
   PWF_HIP(hipEventSynchronize(d->copied));
   loss_grad_descriptors(problems, n, B, psi, y, grad_out, loss_out, ws, L, d->host_desc);
   PWF_HIP(pwf::launch_fill_zero(ws + L.status, 16, st));
   PWF_HIP(hipMemcpyAsync(ws + L.desc, d->host_desc, sizeof(Inst) * n, hipMemcpyHostToDevice, st));
   PWF_HIP(hipEventRecord(d->copied, st));
-  return loss_grad_sequence(Launcher{d->tables, ws, L, B, st}, n);
+  PWF_HIP(pwf::launch_build_tables((const Inst*)(ws + L.desc), n, st));
+  return loss_grad_sequence(Launcher{d->tables, ws, L, B, st});
 }
 
 pwf_status pwf_sync_status(void* workspace, void* stream) {

@@ -151,14 +151,12 @@ int speckle_sum_blocks();
 hipError_t launch_speckle_sums(const float* img, int nx, int ny, int max_shift, double* partial, double* out,
                                hipStream_t st);
 // Joint diffuser step (see joint_update_kernel): normalisation from the S2
-// maxima (u1max is overwritten), then t <- t - eta_t sum_j G_j / sum_j max|u1_j|^2.
+// maxima (u1max is overwritten), then t <- t - eta_t sum_j G_j / sum_j max|u1_j|^2
+// and *maxt2 = max |t|^2.
 hipError_t launch_joint_update(float* u1max, int n, int count, size_t max_stride, const float2* g,
-                               size_t field_stride, size_t m, float2* t, double eta_t, double* dsum,
+                               size_t field_stride, size_t m, float2* t, double eta_t, double* dsum, float* maxt2,
                                hipStream_t st);
-int maxabs2_blocks();
-hipError_t launch_maxabs2(const float2* t, size_t m, float* partial, float* out, hipStream_t st);
-// max |t|^2 of B.n <= kMaxabs2Batch diffusers in two launches; partial holds
-// maxabs2_blocks() floats per diffuser (diffuser d at d * maxabs2_blocks()).
+// max |t|^2 of B.n <= kMaxabs2Batch diffusers, raised from what out[d] holds (0).
 constexpr int kMaxabs2Batch = 32;
 struct Maxabs2Batch {
   const float2* t[kMaxabs2Batch];
@@ -166,7 +164,18 @@ struct Maxabs2Batch {
   float* out[kMaxabs2Batch];
   int32_t n;
 };
-hipError_t launch_maxabs2_batch(const Maxabs2Batch& B, float* partial, hipStream_t st);
+hipError_t launch_maxabs2(const Maxabs2Batch& B, hipStream_t st);
+// Descriptors to device memory, their window tables, and words to clear, in one
+// launch of up to kSetupInsts instances (what the 4 KB of kernel arguments hold).
+constexpr int kSetupInsts = 10;
+struct SetupArgs {
+  Inst inst[kSetupInsts];
+  Inst* dst;
+  uint32_t* words;
+  int32_t clear;
+};
+static_assert(sizeof(SetupArgs) <= 4000, "kernel arguments");
+hipError_t launch_setup(const SetupArgs& A, int n, hipStream_t st);
 
 // Number of float2 twiddles of the N-point row (which = 0), column (1),
 // alternative row (2) or third row (3) plan, forward and reversed; fills

@@ -117,40 +117,30 @@ __global__ void loss_final_kernel(const Inst* __restrict__ insts, int32_t* statu
 
 // ------------------------------------------------------------------ utilities
 
+// Maximum of the workgroup's (256 lanes') non-negative values into *out, which
+// other workgroups raise too.  Order-free, so deterministic.
+__device__ __forceinline__ void block_max_to(float mx, float* out) {
+  __shared__ float red[4];
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    atomicMax((unsigned int*)out, __float_as_uint(mx));
+  }
+}
+
 __global__ void fill_zero_kernel(float4* __restrict__ p, size_t n16) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
     p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// max_r |t_r|^2 of one diffuser: per-block maxima, then the last pass reduces them.
-__global__ void maxabs2_partial(const float2* __restrict__ t, size_t m, float* __restrict__ partial) {
-  float mx = 0.f;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < m; i += (size_t)gridDim.x * blockDim.x) {
-    const float2 a = t[i];
-    mx = fmaxf(mx, a.x * a.x + a.y * a.y);
-  }
-  __shared__ float red[16];
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < (int)(blockDim.x >> 6); ++i) mx = fmaxf(mx, red[i]);
-    partial[blockIdx.x] = fmaxf(mx, red[0]);
-  }
-}
-
-__global__ void maxabs2_final(const float* __restrict__ partial, int np, float* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    float mx = 0.f;
-    for (int i = 0; i < np; ++i) mx = fmaxf(mx, partial[i]);
-    *out = mx;
-  }
-}
-
-// max |t|^2 of up to kMaxabs2Batch diffusers in one launch pair (blockIdx.y =
-// diffuser): the same per-block partials and the same final reduction order
-// as maxabs2_partial / maxabs2_final.
-__global__ void maxabs2_partial_multi(Maxabs2Batch B, float* __restrict__ partial) {
+// max |t|^2 of up to kMaxabs2Batch diffusers (blockIdx.y = diffuser) into out[d],
+// which hold 0 on entry: workgroup maxima, then an integer maximum of their
+// bits (the values are not negative), so no second launch has to wait for the
+// first.  (A launch in which one thread took the maximum of 256 partials was
+// 11 us of every gradient, step and solve.)
+__global__ void __launch_bounds__(256) maxabs2_kernel(Maxabs2Batch B) {
   const int d = blockIdx.y;
   const float2* __restrict__ t = B.t[d];
   const size_t m = B.m[d];
@@ -159,28 +149,11 @@ __global__ void maxabs2_partial_multi(Maxabs2Batch B, float* __restrict__ partia
     const float2 a = t[i];
     mx = fmaxf(mx, a.x * a.x + a.y * a.y);
   }
-  __shared__ float red[16];
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < (int)(blockDim.x >> 6); ++i) mx = fmaxf(mx, red[i]);
-    partial[(size_t)d * gridDim.x + blockIdx.x] = fmaxf(mx, red[0]);
-  }
-}
-
-__global__ void maxabs2_final_multi(Maxabs2Batch B, const float* __restrict__ partial, int np) {
-  if (threadIdx.x == 0) {
-    const int d = blockIdx.x;
-    float mx = 0.f;
-    for (int i = 0; i < np; ++i) mx = fmaxf(mx, partial[(size_t)d * np + i]);
-    *B.out[d] = mx;
-  }
+  block_max_to(mx, B.out[d]);
 }
 
 // 1-D factors of the separable windows of one instance (FP64 arguments).
-__global__ void build_tables_kernel(const Inst* __restrict__ insts) {
-  const Inst I = insts[blockIdx.x];
+__device__ __forceinline__ void build_tables(const Inst& I) {
   for (int k = threadIdx.x; k < I.nx + I.ny; k += blockDim.x) {
     const bool isx = k < I.nx;
     const int kk = isx ? k : k - I.nx;
@@ -223,6 +196,28 @@ __global__ void build_tables_kernel(const Inst* __restrict__ insts) {
       I.gy[kk] = g2;
     }
   }
+}
+
+__global__ void build_tables_kernel(const Inst* __restrict__ insts) { build_tables(insts[blockIdx.x]); }
+
+// Set-up of a call on few instances in one launch: the descriptors come as
+// kernel arguments, so that no copy engine and no staging buffer are involved,
+// and go to device memory for the sweeps; the window tables are built from
+// them, and `clear` 32-bit words at `words` (status flag, maxima) are zeroed.
+__global__ void __launch_bounds__(256) setup_kernel(const SetupArgs A) {
+  const Inst& I = A.inst[blockIdx.x];
+  const uint32_t* src = (const uint32_t*)&I;
+  uint32_t* dst = (uint32_t*)(A.dst + blockIdx.x);
+  for (int i = threadIdx.x; i < (int)(sizeof(Inst) / 4); i += 256) dst[i] = src[i];
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < A.clear; i += 256) A.words[i] = 0u;
+  build_tables(I);
+}
+
+hipError_t launch_setup(const SetupArgs& A, int n, hipStream_t st) {
+  if (n < 1 || n > kSetupInsts) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(setup_kernel, dim3(n), dim3(256), 0, st, A);
+  return hipGetLastError();
 }
 
 hipError_t launch_build_tables(const Inst* insts, int n, hipStream_t st) {
@@ -405,8 +400,6 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
   return hipGetLastError();
 }
 
-int maxabs2_blocks() { return 256; }
-
 // Joint diffuser refinement: normalisation sum_j max|u1_j|^2 from the S2
 // workgroup maxima (n instances, `count` maxima each, `stride` floats apart).
 // One workgroup per instance takes its maximum (order-free, so deterministic)
@@ -424,7 +417,7 @@ __global__ void __launch_bounds__(256) joint_max_kernel(float* __restrict__ u1ma
 }
 
 __global__ void __launch_bounds__(256) joint_norm_kernel(const float* __restrict__ u1max, int n, size_t stride,
-                                                         double* __restrict__ dsum) {
+                                                         double* __restrict__ dsum, float* __restrict__ maxt2) {
   __shared__ float v[256];
   double acc = 0.0;
   for (int j0 = 0; j0 < n; j0 += 256) {  // maxima gathered in parallel, summed in order
@@ -435,33 +428,65 @@ __global__ void __launch_bounds__(256) joint_norm_kernel(const float* __restrict
       for (int j = 0; j < m; ++j) acc += (double)v[j];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *dsum = acc;
+  if (threadIdx.x == 0) {
+    *dsum = acc;
+    *maxt2 = 0.f;   // (this iteration's gradient has read it; joint_update_kernel raises it again)
+  }
+}
+
+__device__ __forceinline__ float4 ld_nt(const float4* p) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const f4 a = __builtin_nontemporal_load((const f4*)p);
+  return make_float4(a.x, a.y, a.z, a.w);
 }
 
 // t <- t - eta_t sum_j G_j / dsum, G_j = conj(u1_j) a2_j of instance j (fields
 // `stride` elements apart); the sum over instances runs in order, in FP64.
-__global__ void joint_update_kernel(const float2* __restrict__ g, int n, size_t stride, size_t m,
-                                    float2* __restrict__ t, double eta_t, const double* __restrict__ dsum) {
+// Two elements per lane and eight instances' loads in flight at a time: bound
+// by reading the n fields (40 x 1024^2: 91 -> 61 us, 5.8 TB/s).  Leaves max |t|^2 of the
+// new t for the next gradient.
+__global__ void __launch_bounds__(256) joint_update_kernel(const float4* __restrict__ g, int n, size_t stride2,
+                                                           size_t m2, float2* __restrict__ t, double eta_t,
+                                                           const double* __restrict__ dsum, float* __restrict__ maxt2) {
   const double scale = eta_t / *dsum;
-  for (size_t r = blockIdx.x * (size_t)blockDim.x + threadIdx.x; r < m; r += (size_t)gridDim.x * blockDim.x) {
-    double gx = 0.0, gy = 0.0;
-    for (int j = 0; j < n; ++j) {
-      const float2 a = g[(size_t)j * stride + r];
-      gx += a.x;
-      gy += a.y;
+  float mx = 0.f;
+  // (a contiguous range of the field per XCD: with the blocks dealt over all of it, 105 us)
+  const unsigned blk = (gridDim.x & 7) ? blockIdx.x : (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  for (size_t r = blk * (size_t)blockDim.x + threadIdx.x; r < m2; r += (size_t)gridDim.x * blockDim.x) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    auto add = [&](float4 a) {
+      s[0] += a.x;
+      s[1] += a.y;
+      s[2] += a.z;
+      s[3] += a.w;
+    };
+    int j = 0;
+    for (; j + 8 <= n; j += 8) {
+      float4 a[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a[u] = ld_nt(g + (size_t)(j + u) * stride2 + r);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) add(a[u]);
     }
-    const float2 tv = t[r];
-    t[r] = make_float2((float)((double)tv.x - scale * gx), (float)((double)tv.y - scale * gy));
+    for (; j < n; ++j) add(ld_nt(g + (size_t)j * stride2 + r));
+    const float2 t0 = t[2 * r], t1 = t[2 * r + 1];   // (the caller's: aligned to 8 bytes only)
+    const float4 w = make_float4((float)((double)t0.x - scale * s[0]), (float)((double)t0.y - scale * s[1]),
+                                 (float)((double)t1.x - scale * s[2]), (float)((double)t1.y - scale * s[3]));
+    t[2 * r] = make_float2(w.x, w.y);
+    t[2 * r + 1] = make_float2(w.z, w.w);
+    mx = fmaxf(mx, fmaxf(w.x * w.x + w.y * w.y, w.z * w.z + w.w * w.w));
   }
+  block_max_to(mx, maxt2);
 }
 
 hipError_t launch_joint_update(float* u1max, int n, int count, size_t max_stride, const float2* g,
-                               size_t field_stride, size_t m, float2* t, double eta_t, double* dsum,
+                               size_t field_stride, size_t m, float2* t, double eta_t, double* dsum, float* maxt2,
                                hipStream_t st) {
   hipLaunchKernelGGL(joint_max_kernel, dim3(n), dim3(256), 0, st, u1max, count, max_stride);
-  hipLaunchKernelGGL(joint_norm_kernel, dim3(1), dim3(256), 0, st, u1max, n, max_stride, dsum);
-  const int blocks = (int)std::min<size_t>((m + 255) / 256, 4096);
-  hipLaunchKernelGGL(joint_update_kernel, dim3(blocks), dim3(256), 0, st, g, n, field_stride, m, t, eta_t, dsum);
+  hipLaunchKernelGGL(joint_norm_kernel, dim3(1), dim3(256), 0, st, u1max, n, max_stride, dsum, maxt2);
+  const int blocks = (int)std::min<size_t>((m / 2 + 255) / 256, 2048);
+  hipLaunchKernelGGL(joint_update_kernel, dim3(blocks), dim3(256), 0, st, (const float4*)g, n, field_stride / 2, m / 2,
+                     t, eta_t, dsum, maxt2);
   return hipGetLastError();
 }
 
@@ -476,7 +501,7 @@ hipError_t launch_joint_update(float* u1max, int n, int count, size_t max_stride
 // nothing is reduced across lanes but sum I and sum I^2.  Bound by the vector
 // ALU (four operations per pixel and wave).  With all 67 sums in every thread
 // the reductions and the one thread that added 512 partials of each sum were
-// 0.21 ms at 1024^2; 0.0SPK now.
+// 0.21 ms at 1024^2; 27 us now.
 constexpr int kSpkCols = 64, kSpkPitch = kSpkCols + kMaxShift + 1;   // (odd: y lanes hit distinct banks)
 constexpr int kSpkValues = 1 + 2 * (kMaxShift + 1);
 
@@ -587,16 +612,9 @@ hipError_t launch_speckle_sums(const float* img, int nx, int ny, int max_shift, 
   return launch_sum_rows(partial, blocks, kSpkValues, out, st);
 }
 
-hipError_t launch_maxabs2_batch(const Maxabs2Batch& B, float* partial, hipStream_t st) {
+hipError_t launch_maxabs2(const Maxabs2Batch& B, hipStream_t st) {
   if (B.n < 1 || B.n > kMaxabs2Batch) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(maxabs2_partial_multi, dim3(maxabs2_blocks(), B.n), dim3(256), 0, st, B, partial);
-  hipLaunchKernelGGL(maxabs2_final_multi, dim3(B.n), dim3(64), 0, st, B, partial, maxabs2_blocks());
-  return hipGetLastError();
-}
-
-hipError_t launch_maxabs2(const float2* t, size_t m, float* partial, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(maxabs2_partial, dim3(maxabs2_blocks()), dim3(256), 0, st, t, m, partial);
-  hipLaunchKernelGGL(maxabs2_final, dim3(1), dim3(64), 0, st, partial, maxabs2_blocks(), out);
+  hipLaunchKernelGGL(maxabs2_kernel, dim3(256, B.n), dim3(256), 0, st, B);
   return hipGetLastError();
 }
 
