@@ -71,7 +71,18 @@ struct Context {
   static constexpr int kForks = 3;
   hipStream_t fork[kForks] = {};
   hipEvent_t fork_ev[kForks + 1] = {};
-  std::map<GraphKey, hipGraphExec_t> graphs;
+  // Captured solve loops.  Each graph is one chain of launches: the size classes
+  // of an uneven batch have a graph each, launched side by side on streams of
+  // their own.  The least recently used one makes room for a new one, once its
+  // last launch has ended (`done`).
+  struct CachedGraph {
+    hipGraphExec_t exec = nullptr;
+    hipEvent_t done = nullptr;
+    uint64_t used = 0;
+  };
+  static constexpr size_t kGraphs = 16;
+  std::map<GraphKey, CachedGraph> graphs;
+  uint64_t graph_uses = 0;
   // pinned staging for descriptor uploads (ring of slots)
   static constexpr int kSlots = 4;
   void* stage[kSlots] = {};
@@ -1089,83 +1100,79 @@ pwf_status joint_step(const Launcher& K, const pwf_problem* probs, int n, const 
   return PWF_OK;
 }
 
-pwf_status solve_sequence(const Launcher& K, const pwf_problem* probs, int n, int iters, const JointCfg& jc) {
-  // spectrum of y (uses W as scratch), then clear W, psi_hat, z_hat of every
-  // instance (contiguous regions): psi = z = 0
+// Spectrum of y (uses W as scratch), then W, psi_hat, z_hat of every instance
+// (contiguous regions) cleared: psi = z = 0.
+pwf_status solve_start(const Launcher& K) {
   PWF_TRY(K.row(pwf::ROW_REAL_FFT));
   PWF_TRY(K.col(pwf::COL_SPEC_YHAT));
   PWF_HIP(pwf::launch_fill_zero(K.ws + K.L.W[K.B.order[0]], K.L.v[K.B.order[0]] - K.L.W[K.B.order[0]], K.st));
+  return PWF_OK;
+}
+
+// The iterations and the final inverse pass of the launcher's classes (one
+// launch per sweep over all of them when it is merged: a sweep whose row plan or
+// tile width the merged kernels do not hold is launched per class).
+pwf_status solve_iterations(const Launcher& K, const pwf_problem* probs, int n, int iters, const JointCfg& jc) {
   const int s0 = K.corr_tol > 0.0 ? pwf::ROW_PSI_UPDATE_CORR : pwf::ROW_PSI_UPDATE;
-  auto iterate = [&](const Launcher& Q) -> pwf_status {
-    for (int k = 0; k < iters; ++k) {
-      PWF_TRY(Q.row(s0, k));
-      PWF_TRY(Q.col(pwf::COL_CHIRP1, k));
-      PWF_TRY(Q.row(pwf::ROW_MUL_T, k));
-      PWF_TRY(Q.col(pwf::COL_CHIRP2, k));
-      PWF_TRY(Q.row(pwf::ROW_INTENSITY, k));
-      PWF_TRY(Q.col(pwf::COL_BLUR_LOSS, k));
-      PWF_TRY(Q.row(pwf::ROW_BACKBLUR, k));
-      PWF_TRY(Q.col(pwf::COL_CHIRP2_CONJ, k));
-      PWF_TRY(Q.row(pwf::ROW_MUL_CONJ_T, k));
-      PWF_TRY(Q.col(pwf::COL_CHIRP1_CONJ, k));
-      PWF_TRY(Q.row(pwf::ROW_GRAD, k));
-      PWF_TRY(Q.col(pwf::COL_NESTEROV, k));
-      if (jc.on) PWF_TRY(joint_step(Q, probs, n, jc));
+  auto row = [&](int op, int k) { return K.merged ? K.row_merged(op, k) : K.row(op, k); };
+  auto col = [&](int op, int k) { return K.merged ? K.col_merged(op, k) : K.col(op, k); };
+  for (int k = 0; k < iters; ++k) {
+    PWF_TRY(row(s0, k));
+    PWF_TRY(col(pwf::COL_CHIRP1, k));
+    PWF_TRY(row(pwf::ROW_MUL_T, k));
+    PWF_TRY(col(pwf::COL_CHIRP2, k));
+    PWF_TRY(row(pwf::ROW_INTENSITY, k));
+    PWF_TRY(col(pwf::COL_BLUR_LOSS, k));
+    PWF_TRY(row(pwf::ROW_BACKBLUR, k));
+    PWF_TRY(col(pwf::COL_CHIRP2_CONJ, k));
+    PWF_TRY(row(pwf::ROW_MUL_CONJ_T, k));
+    PWF_TRY(col(pwf::COL_CHIRP1_CONJ, k));
+    PWF_TRY(row(pwf::ROW_GRAD, k));
+    PWF_TRY(col(pwf::COL_NESTEROV, k));
+    if (jc.on) PWF_TRY(joint_step(K, probs, n, jc));
+  }
+  return K.row(pwf::ROW_IFFT_OUT, iters);
+}
+
+// Launch the graph of `key` on `s`, captured by `enqueue(stream)` if it is not cached.
+template <class F>
+pwf_status launch_graph(Context& c, const GraphKey& key, hipStream_t s, F enqueue) {
+  auto it = c.graphs.find(key);
+  if (it == c.graphs.end()) {
+    while (c.graphs.size() >= Context::kGraphs) {
+      auto old = c.graphs.begin();
+      for (auto g = c.graphs.begin(); g != c.graphs.end(); ++g)
+        if (g->second.used < old->second.used) old = g;
+      (void)hipEventSynchronize(old->second.done);   // a launch in flight keeps using the graph
+      (void)hipGraphExecDestroy(old->second.exec);
+      (void)hipEventDestroy(old->second.done);
+      c.graphs.erase(old);
     }
-    PWF_TRY(Q.row(pwf::ROW_IFFT_OUT, iters));
-    return PWF_OK;
-  };
-  const int nc = (int)K.B.classes.size();
-  if (nc <= 1 || jc.on) return iterate(K);
-  if (K.merged) {
-    // One launch per sweep over every size class (a sweep whose row plan or
-    // tile width the merged kernels do not hold is launched per class).
-    for (int k = 0; k < iters; ++k) {
-      PWF_TRY(K.row_merged(s0, k));
-      PWF_TRY(K.col_merged(pwf::COL_CHIRP1, k));
-      PWF_TRY(K.row_merged(pwf::ROW_MUL_T, k));
-      PWF_TRY(K.col_merged(pwf::COL_CHIRP2, k));
-      PWF_TRY(K.row_merged(pwf::ROW_INTENSITY, k));
-      PWF_TRY(K.col_merged(pwf::COL_BLUR_LOSS, k));
-      PWF_TRY(K.row_merged(pwf::ROW_BACKBLUR, k));
-      PWF_TRY(K.col_merged(pwf::COL_CHIRP2_CONJ, k));
-      PWF_TRY(K.row_merged(pwf::ROW_MUL_CONJ_T, k));
-      PWF_TRY(K.col_merged(pwf::COL_CHIRP1_CONJ, k));
-      PWF_TRY(K.row_merged(pwf::ROW_GRAD, k));
-      PWF_TRY(K.col_merged(pwf::COL_NESTEROV, k));
+    hipGraph_t graph = nullptr;
+    Context::CachedGraph g;
+    PWF_HIP(hipStreamBeginCapture(c.side, hipStreamCaptureModeThreadLocal));
+    const pwf_status cs = enqueue(c.side);
+    const hipError_t ee = hipStreamEndCapture(c.side, &graph);
+    if (cs != PWF_OK || ee != hipSuccess) {
+      if (graph) (void)hipGraphDestroy(graph);
+      return cs != PWF_OK ? cs : PWF_ERR_HIP;
     }
-    PWF_TRY(K.row(pwf::ROW_IFFT_OUT, iters));
-    return PWF_OK;
+    const hipError_t ie = hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(graph);
+    PWF_HIP(ie);
+    if (hipEventCreateWithFlags(&g.done, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGraphExecDestroy(g.exec);
+      return PWF_ERR_HIP;
+    }
+    it = c.graphs.emplace(key, g).first;
   }
-  // The size classes of an uneven batch are independent problems: their
-  // iterations run on parallel streams (classes dealt round-robin), forked
-  // from and joined back into K.st with events, so that a small class's short
-  // launches overlap the large ones instead of alternating with them.
-  const int ns = std::min(nc, Context::kForks + 1);
-  std::vector<Batch> subs(ns);
-  for (int c = 0; c < nc; ++c) {
-    subs[c % ns].order = K.B.order;
-    subs[c % ns].classes.push_back(K.B.classes[c]);
-  }
-  PWF_HIP(hipEventRecord(K.ctx.fork_ev[0], K.st));
-  for (int j = 1; j < ns; ++j) PWF_HIP(hipStreamWaitEvent(K.ctx.fork[j - 1], K.ctx.fork_ev[0], 0));
-  for (int j = 0; j < ns; ++j) {
-    Launcher Kj{K.ctx, K.ws, K.L, subs[j], j == 0 ? K.st : K.ctx.fork[j - 1]};
-    Kj.corr_tol = K.corr_tol;
-    PWF_TRY(iterate(Kj));
-  }
-  for (int j = 1; j < ns; ++j) {
-    PWF_HIP(hipEventRecord(K.ctx.fork_ev[j], K.ctx.fork[j - 1]));
-    PWF_HIP(hipStreamWaitEvent(K.st, K.ctx.fork_ev[j], 0));
-  }
+  it->second.used = ++c.graph_uses;
+  PWF_HIP(hipGraphLaunch(it->second.exec, s));
+  PWF_HIP(hipEventRecord(it->second.done, s));
   return PWF_OK;
 }
 
 }  // namespace
-
-extern "C" {
-
-}  // extern "C"
 
 namespace {
 
@@ -1219,15 +1226,17 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
   if (iters_done)
     for (int i = 0; i < n; ++i) iters_done[i] = iters;
 
-  auto enqueue = [&](hipStream_t s) -> pwf_status {
-    Launcher K{*ctx, ws, L, B, s};
+  auto launcher = [&](const Batch& b, hipStream_t s) {
+    Launcher K{*ctx, ws, L, b, s};
     K.corr_tol = corr_tol;
     K.merged = merged;
+    return K;
+  };
+  auto start = [&](hipStream_t s) -> pwf_status {
     if (corr_mode) PWF_HIP(pwf::launch_fill_zero(ws + L.stop, align_up(sizeof(int32_t) * n), s));
     PWF_TRY(launch_maxt2(problems, n, B, desc, s));
-    return solve_sequence(K, problems, n, iters, jc);
+    return solve_start(launcher(B, s));
   };
-
   auto report = [&]() -> pwf_status {
     if (!corr_mode || !iters_done) return PWF_OK;
     std::vector<int32_t> stop(n);
@@ -1236,11 +1245,6 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
     for (int i = 0; i < n; ++i) iters_done[i] = stop[i] > 0 ? stop[i] : iters;
     return PWF_OK;
   };
-
-  if (!g_graph_mode) {
-    PWF_TRY(enqueue(st));
-    return report();
-  }
 
   GraphKey key{workspace, n, iters, {}};
   key.dims.push_back(corr_mode ? 1 : 0);
@@ -1261,34 +1265,58 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
     key.dims.push_back((int)(((uintptr_t)p.diffuser) & 0x7fffffff));
     key.dims.push_back((int)(((uintptr_t)p.diffuser) >> 31));
   }
-  hipGraphExec_t exec = nullptr;
-  auto it = ctx->graphs.find(key);
-  if (it != ctx->graphs.end()) {
-    exec = it->second;
-  } else {
-    hipGraph_t graph = nullptr;
-    PWF_HIP(hipStreamBeginCapture(ctx->side, hipStreamCaptureModeThreadLocal));
-    const pwf_status cs = enqueue(ctx->side);
-    const hipError_t ee = hipStreamEndCapture(ctx->side, &graph);
-    if (cs != PWF_OK) {
-      if (graph) (void)hipGraphDestroy(graph);
-      return cs;
+
+  const int nc = (int)B.classes.size();
+  if (nc <= 1 || jc.on || merged) {
+    auto all = [&](hipStream_t s) -> pwf_status {
+      PWF_TRY(start(s));
+      return solve_iterations(launcher(B, s), problems, n, iters, jc);
+    };
+    if (!g_graph_mode) {
+      PWF_TRY(all(st));
+      return report();
     }
-    PWF_HIP(ee);
-    const hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(graph);
-    PWF_HIP(ie);
-    if (ctx->graphs.size() >= 8) {
-      (void)hipGraphExecDestroy(ctx->graphs.begin()->second);
-      ctx->graphs.erase(ctx->graphs.begin());
-    }
-    ctx->graphs[key] = exec;
+    PWF_HIP(hipEventRecord(ctx->ev_in, st));
+    PWF_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_in, 0));
+    PWF_TRY(launch_graph(*ctx, key, ctx->side, all));
+    PWF_HIP(hipEventRecord(ctx->ev_out, ctx->side));
+    PWF_HIP(hipStreamWaitEvent(st, ctx->ev_out, 0));
+    return report();
   }
-  PWF_HIP(hipEventRecord(ctx->ev_in, st));
-  PWF_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_in, 0));
-  PWF_HIP(hipGraphLaunch(exec, ctx->side));
-  PWF_HIP(hipEventRecord(ctx->ev_out, ctx->side));
-  PWF_HIP(hipStreamWaitEvent(st, ctx->ev_out, 0));
+
+  // The size classes of an uneven batch are independent problems: after the
+  // common start their iterations run on parallel streams (classes dealt
+  // round-robin), forked from and joined back into st with events, so that a
+  // small class's short launches overlap the large ones instead of alternating
+  // with them.  Each class is a graph of its own: one graph with the classes as
+  // branches took longer, and the runtime has ended in a fault where such graphs
+  // were made and dropped in turn.
+  PWF_TRY(start(st));
+  PWF_HIP(hipEventRecord(ctx->fork_ev[0], st));
+  const int ns = std::min(nc, Context::kForks + 1);
+  // (the largest on `side`: with the smallest there 24 x 512^2 + 32 x 1024^2 + 8 x 2048^2 took 2% longer)
+  auto stream_of = [&](int c) { return (nc - 1 - c) % ns == 0 ? ctx->side : ctx->fork[(nc - 1 - c) % ns - 1]; };
+  for (int j = 0; j < ns; ++j) PWF_HIP(hipStreamWaitEvent(stream_of(j), ctx->fork_ev[0], 0));
+  pwf_status rc = PWF_OK;
+  for (int c = nc - 1; c >= 0 && rc == PWF_OK; --c) {   // the largest class first
+    Batch one;
+    one.order = B.order;
+    one.classes = {B.classes[c]};
+    auto iterations = [&](hipStream_t s) { return solve_iterations(launcher(one, s), problems, n, iters, jc); };
+    if (g_graph_mode) {
+      GraphKey ck = key;
+      ck.dims.push_back(c);
+      rc = launch_graph(*ctx, ck, stream_of(c), iterations);
+    } else {
+      rc = iterations(stream_of(c));
+    }
+  }
+  for (int j = 0; j < ns; ++j) {   // (also after an error: what was launched still uses the workspace)
+    hipEvent_t e = j == 0 ? ctx->ev_out : ctx->fork_ev[j];
+    PWF_HIP(hipEventRecord(e, stream_of(j)));
+    PWF_HIP(hipStreamWaitEvent(st, e, 0));
+  }
+  PWF_TRY(rc);
   return report();
 }
 
@@ -2206,7 +2234,11 @@ void pwf_finalize(void) {
   std::lock_guard<std::mutex> lk(g_mu);
   for (Context& c : g_ctx) {
     if (!c.ready) continue;
-    for (auto& kv : c.graphs) (void)hipGraphExecDestroy(kv.second);
+    for (auto& kv : c.graphs) {
+      (void)hipEventSynchronize(kv.second.done);
+      (void)hipGraphExecDestroy(kv.second.exec);
+      (void)hipEventDestroy(kv.second.done);
+    }
     c.graphs.clear();
     for (float2*& t : c.tw) {
       if (t) (void)hipFree(t);
