@@ -88,6 +88,28 @@ __device__ __forceinline__ void gst(float2* p, uint32_t i, float2 a) {
   v.y = a.y;
   *(pwf_gfv2*)((char*)p + (i << 3)) = v;
 }
+// Non-temporal variants, for fields that are next touched several sweeps later
+// (x, v, Z, the data spectrum): kept out of the caches' favour, they leave room
+// for the work field, which the next sweep reads.  180 x 1024^2: 88.7 -> 86.7 ms
+// for 10 iterations.
+__device__ __forceinline__ float2 gld_nt(const float2* p, uint32_t i) {
+  const pwf_fv2 v = __builtin_nontemporal_load((const pwf_gfv2*)((const char*)p + (i << 3)));
+  return make_float2(v.x, v.y);
+}
+__device__ __forceinline__ void gst_nt(float2* p, uint32_t i, float2 a) {
+  pwf_fv2 v;
+  v.x = a.x;
+  v.y = a.y;
+  __builtin_nontemporal_store(v, (pwf_gfv2*)((char*)p + (i << 3)));
+}
+template <bool NT> __device__ __forceinline__ float2 gld_if_nt(const float2* p, uint32_t i) {
+  if constexpr (NT) return gld_nt(p, i);
+  else return gld(p, i);
+}
+template <bool NT> __device__ __forceinline__ void gst_if_nt(float2* p, uint32_t i, float2 a) {
+  if constexpr (NT) gst_nt(p, i, a);
+  else gst(p, i, a);
+}
 __device__ __forceinline__ float gldf(const float* p, uint32_t i) { return *(const pwf_gf*)((const char*)p + (i << 2)); }
 __device__ __forceinline__ void gstf(float* p, uint32_t i, float a) { *(pwf_gf*)((char*)p + (i << 2)) = a; }
 

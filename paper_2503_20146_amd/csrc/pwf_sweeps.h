@@ -355,7 +355,7 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
       static_for<0, E / R1>([&](auto cc) {
         static_for<0, R1>([&](auto qq) {
           constexpr int c = decltype(cc)::value, q = decltype(qq)::value;
-          side[c * R1 + q] = gld(sp, sb + t + T * c + q * M1);
+          side[c * R1 + q] = T_SIDE ? gld(sp, sb + t + T * c + q * M1) : gld_nt(sp, sb + t + T * c + q * M1);
         });
       });
     }
@@ -462,10 +462,10 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
           n_old += (double)xo.x * xo.x + (double)xo.y * xo.y;
         }
         v[e] = xn;
-        if (I.x) gst(I.x, midx, v[e]);
+        if (I.x) gst_nt(I.x, midx, v[e]);
       } else if constexpr (OP == ROW_START) {
         v[e] = cexp_f(v[e]);
-        if (I.x) gst(I.x, midx, v[e]);
+        if (I.x) gst_nt(I.x, midx, v[e]);
       } else if constexpr (OP == ROW_MUL_T) {
         if (I.u1) {  // joint diffuser mode: keep u1 for the diffuser gradient of S8
           gst(I.u1, idx, v[e]);
@@ -475,7 +475,7 @@ __device__ __forceinline__ void row_body(const Sweep& S, int b, float2* lds, flo
       } else if constexpr (OP == ROW_MUL_CONJ_T) {
         v[e] = cmulc(v[e], side[e]);
       } else if constexpr (OP == ROW_INTENSITY) {
-        if (I.v) gst(I.v, midx, v[e]);
+        if (I.v) gst_nt(I.v, midx, v[e]);
         v[e] = make_float2(v[e].x * v[e].x + v[e].y * v[e].y, 0.f);
       } else if constexpr (OP == ROW_BACKBLUR) {
         const float h = v[e].x;
@@ -683,6 +683,10 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
   constexpr int R1 = Plan::radix[0], RL = Plan::radix[Plan::NPASS - 1];
   constexpr int M1 = NF / R1, ML = NF / RL;
   constexpr int NT = T * W;
+  // Z and the data spectrum past the caches where a tile's rows are whole lines
+  // (16 columns, 128 bytes): the other part of a line that 8 columns read half of
+  // is wanted by the neighbour.
+  constexpr bool PAST = W >= 16;
   __shared__ double red[(NT + 63) / 64];
 
   const int inst = b >> S.lg_blocks;
@@ -814,8 +818,8 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
       static_for<0, NA>([&](auto uu) {
         constexpr int u = decltype(uu)::value, e = decltype(bb)::value * NA + u;
         const int j = t + T * (e / RL) + (e % RL) * ML;
-        zk[e] = gld(z_cur, o_a + (uint32_t)((j - t) * nx));
-        zp[slot][u] = gld(z_old, o_a + (uint32_t)((j - t) * nx));
+        zk[e] = gld_if_nt<PAST>(z_cur, o_a + (uint32_t)((j - t) * nx));
+        zp[slot][u] = gld_if_nt<PAST>(z_old, o_a + (uint32_t)((j - t) * nx));
         gb[slot][u] = ytab(j).x;
       });
     };
@@ -850,7 +854,7 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
       const float2 hm = lm.at(mirror_pos(kl));
       const float2 z = make_float2(v[e].x - I.eta * hm.x, v[e].y + I.eta * hm.y);  // - eta conj(h(-k))
       const float2 pn = make_float2(z.x + bf * (z.x - zk[e].x), z.y + bf * (z.y - zk[e].y));
-      gst(z_old, o_up + (uint32_t)((j - t) * nx), z);  // Z_{k+1}; this lane read Z_{k-1} here above
+      gst_if_nt<PAST>(z_old, o_up + (uint32_t)((j - t) * nx), z);  // Z_{k+1}; this lane read Z_{k-1} here above
       v[e] = cscale(pn, I.inv_m);
     });
     __syncthreads();
@@ -950,7 +954,7 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
           v[e] = cscale(v[e], h / (h * h + I.wiener_eps) * I.inv_m);
         } else if constexpr (OP == COL_BLUR_LOSS) {
           const float h = ixv * ytab(j).x;
-          const float2 yh = gld(I.y_hat, o_e);
+          const float2 yh = gld_if_nt<PAST>(I.y_hat, o_e);
           const float2 rr = make_float2(h * v[e].x - yh.x, h * v[e].y - yh.y);
           acc += wgt * ((double)rr.x * (double)rr.x + (double)rr.y * (double)rr.y);
           v[e] = cscale(rr, h * I.inv_m);
