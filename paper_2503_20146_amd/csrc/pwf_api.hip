@@ -343,8 +343,7 @@ std::vector<int> batch_order(const pwf_problem* probs, int n) {
   return order;
 }
 
-// Region order keeps W, psi_hat and z_hat of all instances contiguous so that
-// one fill kernel clears them; within a region the fields follow batch order.
+// The fields of a region lie one after the other, in batch order.
 Layout make_layout(const pwf_problem* probs, int n, bool joint = false) {
   Layout L;
   size_t off = 0;
@@ -556,6 +555,7 @@ struct Launcher {
   bool merged = false;   // batch_merged(B): one launch per sweep over the classes
   bool latency = false;  // the latency plans, where nothing is set (forward calls)
   int width_of(const Class& c, int op) const {
+    if (op == pwf::COL_NESTEROV_FIRST || op == pwf::COL_NESTEROV_SECOND) op = pwf::COL_NESTEROV;
     const bool set = g_col_width[size_index(c.ny)][op] != 0;
     return latency && !set && pwf::latency_shape(c.nx, c.ny, c.count) ? pwf::kLatencyWidth : col_width(c.ny, op);
   }
@@ -1100,24 +1100,27 @@ pwf_status joint_step(const Launcher& K, const pwf_problem* probs, int n, const 
   return PWF_OK;
 }
 
-// Spectrum of y (uses W as scratch), then W, psi_hat, z_hat of every instance
-// (contiguous regions) cleared: psi = z = 0.
+// Spectrum of y (uses W as scratch).
 pwf_status solve_start(const Launcher& K) {
   PWF_TRY(K.row(pwf::ROW_REAL_FFT));
-  PWF_TRY(K.col(pwf::COL_SPEC_YHAT));
-  PWF_HIP(pwf::launch_fill_zero(K.ws + K.L.W[K.B.order[0]], K.L.v[K.B.order[0]] - K.L.W[K.B.order[0]], K.st));
-  return PWF_OK;
+  return K.col(pwf::COL_SPEC_YHAT);
 }
 
 // The iterations and the final inverse pass of the launcher's classes (one
 // launch per sweep over all of them when it is merged: a sweep whose row plan or
 // tile width the merged kernels do not hold is launched per class).
+// The solve starts from psi = Z_0 = Z_{-1} = 0, which no memory has to hold: the
+// first S0 is the start sweep without an input, and S11 reads no state in the
+// first iteration and Z_k only in the second (clearing the three fields and
+// reading them was 2% of ten iterations).
 pwf_status solve_iterations(const Launcher& K, const pwf_problem* probs, int n, int iters, const JointCfg& jc) {
   const int s0 = K.corr_tol > 0.0 ? pwf::ROW_PSI_UPDATE_CORR : pwf::ROW_PSI_UPDATE;
+  if (iters == 0)   // psi = 0, by the final pass
+    PWF_HIP(pwf::launch_fill_zero(K.ws + K.L.W[K.B.order[0]], K.L.psi_hat[K.B.order[0]] - K.L.W[K.B.order[0]], K.st));
   auto row = [&](int op, int k) { return K.merged ? K.row_merged(op, k) : K.row(op, k); };
   auto col = [&](int op, int k) { return K.merged ? K.col_merged(op, k) : K.col(op, k); };
   for (int k = 0; k < iters; ++k) {
-    PWF_TRY(row(s0, k));
+    PWF_TRY(k == 0 ? K.row(pwf::ROW_START) : row(s0, k));
     PWF_TRY(col(pwf::COL_CHIRP1, k));
     PWF_TRY(row(pwf::ROW_MUL_T, k));
     PWF_TRY(col(pwf::COL_CHIRP2, k));
@@ -1128,7 +1131,9 @@ pwf_status solve_iterations(const Launcher& K, const pwf_problem* probs, int n, 
     PWF_TRY(row(pwf::ROW_MUL_CONJ_T, k));
     PWF_TRY(col(pwf::COL_CHIRP1_CONJ, k));
     PWF_TRY(row(pwf::ROW_GRAD, k));
-    PWF_TRY(col(pwf::COL_NESTEROV, k));
+    if (k == 0) PWF_TRY(K.col(pwf::COL_NESTEROV_FIRST));
+    else if (k == 1) PWF_TRY(K.col(pwf::COL_NESTEROV_SECOND, 1));
+    else PWF_TRY(col(pwf::COL_NESTEROV, k));
     if (jc.on) PWF_TRY(joint_step(K, probs, n, jc));
   }
   return K.row(pwf::ROW_IFFT_OUT, iters);

@@ -673,7 +673,9 @@ constexpr bool col_op_ystage(int op) { return col_op_chirp(op) || op == COL_NEST
 // instance run the even-ky half (rows 0 .. NY/2 - 1) and [B/2, B) the odd
 // half, over the same tiles; elements are addressed by their position j in
 // the half-column (row part NY/2 + j) and the frequency is ky = 2 j + part.
-template <int NY, int W, int OP>
+// ZEROS (COL_NESTEROV): how many of the two states Z_{k-1} and Z_k are zero and
+// not read, in the first two iterations of a solve.
+template <int NY, int W, int OP, int ZEROS = 0>
 __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, float2* twl, float2* qyl) {
   constexpr bool SPLIT = col_split<NY>();
   constexpr int NF = col_fft_len<NY>();
@@ -818,8 +820,9 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
       static_for<0, NA>([&](auto uu) {
         constexpr int u = decltype(uu)::value, e = decltype(bb)::value * NA + u;
         const int j = t + T * (e / RL) + (e % RL) * ML;
-        zk[e] = gld_if_nt<PAST>(z_cur, o_a + (uint32_t)((j - t) * nx));
-        zp[slot][u] = gld_if_nt<PAST>(z_old, o_a + (uint32_t)((j - t) * nx));
+        zk[e] = zp[slot][u] = make_float2(0.f, 0.f);
+        if constexpr (ZEROS < 2) zk[e] = gld_if_nt<PAST>(z_cur, o_a + (uint32_t)((j - t) * nx));
+        if constexpr (ZEROS < 1) zp[slot][u] = gld_if_nt<PAST>(z_old, o_a + (uint32_t)((j - t) * nx));
         gb[slot][u] = ytab(j).x;
       });
     };
@@ -994,7 +997,7 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
 
 template <int NY, int W> constexpr int col_threads() { return ColPlanSel<col_fft_len<NY>(), W>::T * W; }
 
-template <int NY, int W, int OP>
+template <int NY, int W, int OP, int ZEROS = 0>
 __global__ void __launch_bounds__((col_threads<NY, W>()), (col_min_waves<NY, W, OP>())) col_sweep(Sweep S) {
   __shared__ float2 lds[ColLds<NY, W>::kExchange];
   __shared__ float2 twl[ColLds<NY, W>::kTwiddles];
@@ -1002,7 +1005,7 @@ __global__ void __launch_bounds__((col_threads<NY, W>()), (col_min_waves<NY, W, 
   // Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a
   // contiguous range of tiles so that tiles sharing 128-byte lines meet in
   // the same L2.
-  col_body<NY, W, OP>(S, xcd_contiguous<true>(blockIdx.x, gridDim.x), lds, twl, qyl);
+  col_body<NY, W, OP, ZEROS>(S, xcd_contiguous<true>(blockIdx.x, gridDim.x), lds, twl, qyl);
 }
 
 // ------------------------------------------------------------------ plain path kernels
@@ -1154,6 +1157,8 @@ hipError_t launch_col_nw(int op, int nblocks, const Sweep& S, hipStream_t st) {
     PWF_CASE(COL_CHIRP1) PWF_CASE(COL_CHIRP2) PWF_CASE(COL_CHIRP2_CONJ) PWF_CASE(COL_CHIRP1_CONJ)
     PWF_CASE(COL_BLUR_LOSS) PWF_CASE(COL_BLUR) PWF_CASE(COL_NESTEROV) PWF_CASE(COL_DIRECTION)
     PWF_CASE(COL_SPEC_YHAT) PWF_CASE(COL_SPEC_PSIHAT) PWF_CASE(COL_WIENER)
+    case COL_NESTEROV_SECOND: hipLaunchKernelGGL((col_sweep<N, W, COL_NESTEROV, 1>), grid, block, 0, st, S); break;
+    case COL_NESTEROV_FIRST: hipLaunchKernelGGL((col_sweep<N, W, COL_NESTEROV, 2>), grid, block, 0, st, S); break;
 #undef PWF_CASE
     default: return hipErrorInvalidValue;
   }
