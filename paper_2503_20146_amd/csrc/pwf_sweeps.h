@@ -201,6 +201,9 @@ __device__ __forceinline__ int xcd_contiguous(int b, int g) {
 
 // Waves per SIMD the compiler must leave room for (launch bound).
 template <int NX, int OP> constexpr int row_min_waves() {
+  // (x t at 2048: without the bound its 32 elements per lane take more than 256
+  // registers, one wave per SIMD: 36 x 2048^2 1.04 ms, with it 0.65)
+  if constexpr (NX >= 2048 && OP == ROW_MUL_T) return 2;
   return (OP == ROW_PSI_UPDATE || OP == ROW_PSI_UPDATE_CORR) ? 3 : OP == ROW_GRAD ? (NX >= 2048 ? 2 : 3) : 4;
 }
 
