@@ -1892,7 +1892,9 @@ bool fbp_layout(int n_proj, int nx, int ny, FbpLayout* L) {
   if (size_index(n_pad) < 0) return false;
   size_t off = 0;
   L->q = off;
-  off += align_up(sizeof(float2) * (size_t)n_proj * ny * fbp_pitch(nx));
+  // (room for rows of the padded length, as the size function has always answered;
+  // the filtered rows, fbp_pitch apart, use the first part of it)
+  off += align_up(sizeof(float2) * (size_t)n_proj * ny * n_pad);
   L->ramp = off;
   off += align_up(sizeof(float) * n_pad);
   L->cs = off;
