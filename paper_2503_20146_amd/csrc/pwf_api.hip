@@ -160,17 +160,19 @@ int g_merge_mode = 0;
 // the caller or the autotuner), else by the size of the batch.
 // - 1024-point columns, up to 10 M pixels: 8 columns instead of 16, twice the
 //   workgroups, where a launch has few waves of them or its fields fit the caches
-//   (S1, S5, S11 in us, 16 -> 8 columns: one field 9.3, 9.8, 14.7 -> 8.3, 7.7,
-//   11.7; nine 33.6, 24.0, 67.5 -> 30.1, 22.3, 64.0; sixteen 52, 42.7, 108 -> 51,
-//   36.1, 140: half lines of fields from memory, read twice, cost more).
+//   (S1, S11 in us, 16 -> 8 columns: one field 9.3, 14.7 -> 8.3, 11.7; nine 33.6,
+//   67.5 -> 30.1, 64.0; sixteen 52, 108 -> 51, 140: half lines of fields from
+//   memory, read twice, cost more).  Not S5, though it would gain as much: its loss
+//   partials are one per tile, and the loss of an instance keeps its bits in
+//   every batch.
 // - S11 of 2048-point columns, from 16 M pixels: 16 columns instead of 8, whole
 //   lines (4 fields 155 -> 132 us, 36 fields 1.42 -> 1.27 ms; 2 fields 56 -> 72: too
 //   few workgroups).
 // (Merged launches hold one width per side, the default.)
 int class_col_width(int nx, int ny, int count, int op) {
   const long long pixels = (long long)nx * ny * count;
-  const bool iteration = op == pwf::COL_CHIRP1 || op == pwf::COL_CHIRP2 || op == pwf::COL_BLUR_LOSS ||
-                         op == pwf::COL_CHIRP2_CONJ || op == pwf::COL_CHIRP1_CONJ || op == pwf::COL_NESTEROV;
+  const bool iteration = op == pwf::COL_CHIRP1 || op == pwf::COL_CHIRP2 || op == pwf::COL_CHIRP2_CONJ ||
+                         op == pwf::COL_CHIRP1_CONJ || op == pwf::COL_NESTEROV;
   if (iteration && !g_merge_mode && g_col_width[size_index(ny)][op] == 0) {
     if (ny == 1024 && pixels <= 10 << 20) return 8;
     if (ny == 2048 && op == pwf::COL_NESTEROV && pixels >= 16 << 20) return 16;
@@ -333,9 +335,8 @@ int col_blocks(int nx, int ny, int op, int width) {
   return (pwf::col_op_half(op) ? nx / 2 : nx) / width * (pwf::col_split_n(ny) ? 2 : 1);
 }
 // loss partials: one per workgroup of the residual sweep
-int n_partials(const pwf_problem& p, int count) {
-  const int nx = p.geom.nx, ny = p.geom.ny;
-  return col_blocks(nx, ny, pwf::COL_BLUR_LOSS, class_col_width(nx, ny, count, pwf::COL_BLUR_LOSS));
+int n_partials(const pwf_problem& p) {
+  return col_blocks(p.geom.nx, p.geom.ny, pwf::COL_BLUR_LOSS, col_width(p.geom.ny, pwf::COL_BLUR_LOSS));
 }
 // room for per-workgroup partials of a column sweep at the narrowest compiled tile
 int max_partials(const pwf_problem& p) {
@@ -464,14 +465,13 @@ Layout make_loss_grad_layout(const pwf_problem* probs, int n) {
 
 // ------------------------------------------------------------------ descriptors
 
-// (count: instances of this grid shape in the batch)
-Inst base_inst(const pwf_problem& p, int count) {
+Inst base_inst(const pwf_problem& p) {
   Inst I;
   std::memset(&I, 0, sizeof(I));
   const pwf_geometry& g = p.geom;
   I.nx = g.nx;
   I.ny = g.ny;
-  I.n_partials = n_partials(p, count);
+  I.n_partials = n_partials(p);
   I.t = (const float2*)p.diffuser;
   const double p2 = g.pixel_m * g.pixel_m;
   I.chirp1_rev = g.z1_m * g.wavelength_m / (2.0 * p2);
@@ -540,11 +540,6 @@ struct Class {
 struct Batch {
   std::vector<int> order;  // descriptor slot -> caller index
   std::vector<Class> classes;
-  int count(const pwf_problem& p) const {   // instances of p's grid shape
-    for (const Class& c : classes)
-      if (c.nx == p.geom.nx && c.ny == p.geom.ny) return c.count;
-    return 0;
-  }
 };
 
 Batch group(const pwf_problem* probs, int n) {
@@ -833,7 +828,7 @@ pwf_status forward_impl(const pwf_problem* problems, int32_t n, const void* cons
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.psi_src = (const float2*)psi[i];
@@ -874,7 +869,7 @@ void loss_grad_descriptors(const pwf_problem* problems, int32_t n, const Batch& 
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -947,7 +942,7 @@ pwf_status pwf_gradient(const pwf_problem* problems, int32_t n, const void* cons
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -1031,7 +1026,7 @@ pwf_status pwf_state_init(const pwf_problem* problems, int32_t n, pwf_state* sta
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.y = y[i];
@@ -1072,7 +1067,7 @@ pwf_status pwf_step(const pwf_problem* problems, int32_t n, pwf_state* states, d
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.k0 = states[i].k;
     I.W = (float2*)(ws + L.W[i]);
@@ -1232,7 +1227,7 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -1400,7 +1395,7 @@ pwf_status pwf_bench_sweep(const pwf_problem* problems, int32_t n, int32_t sweep
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -1484,7 +1479,7 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
   for (int s = 0; s < n; ++s) {
     const int i = B.order[s];
     Inst& I = desc[s];
-    I = base_inst(problems[i], B.count(problems[i]));
+    I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
@@ -1717,7 +1712,7 @@ pwf_status pwf_solve_plain(const pwf_problem* problem, const float* y, void* psi
   const pwf_problem& p = *problem;
   const int nx = p.geom.nx, ny = p.geom.ny;
   const size_t m = (size_t)nx * ny;
-  Inst I = base_inst(p, 1);
+  Inst I = base_inst(p);
   attach_tables(I, ws, L, 0);
   I.y = y;
   I.maxt2 = (const float*)(ws + L.maxt2);
@@ -1847,7 +1842,7 @@ pwf_status pwf_diffuser_from_reference(const pwf_problem* problem, const float* 
   PWF_TRY(context_for_current(&ctx));
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  Inst I = base_inst(*problem, 1);
+  Inst I = base_inst(*problem);
   attach_tables(I, ws, L, 0);
   I.W = (float2*)(ws + L.W[0]);
   I.y = ref;
