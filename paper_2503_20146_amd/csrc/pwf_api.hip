@@ -1858,7 +1858,7 @@ pwf_status pwf_diffuser_from_reference(const pwf_problem* problem, const float* 
   PWF_TRY(K.row(pwf::ROW_REAL_FULL));
   PWF_TRY(K.col(pwf::COL_WIENER));
   PWF_TRY(K.row(pwf::ROW_SQRT_POS));
-  PWF_TRY(K.col(pwf::COL_CHIRP2_CONJ));
+  PWF_TRY(K.col(pwf::COL_BACK_L2));
   PWF_TRY(K.row(pwf::ROW_IFFT_OUT));
   return PWF_OK;
 }

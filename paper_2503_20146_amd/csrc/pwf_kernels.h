@@ -58,6 +58,7 @@ enum ColOp {
   COL_SPEC_YHAT,       // y_hat = FFT_y(W)
   COL_SPEC_PSIHAT,     // psi_hat = FFT_y(W); z_hat = psi_hat
   COL_WIENER,          // x IOTF / (IOTF^2 + wiener_eps) (calibration)
+  COL_BACK_L2,         // x conj Q_L2, each factor from one FP64 phase (calibration)
   COL_NESTEROV_FIRST,  // S11 of a solve's first iteration: Z_k = Z_{k-1} = 0, not read
   COL_NESTEROV_SECOND, // S11 of its second: Z_{k-1} = 0, not read
 };

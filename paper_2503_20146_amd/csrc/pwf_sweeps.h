@@ -617,6 +617,7 @@ PWF_COL_TRAIT(COL_CHIRP1_CONJ, true)
 PWF_COL_TRAIT(COL_BLUR_LOSS, true)
 PWF_COL_TRAIT(COL_BLUR, true)
 PWF_COL_TRAIT(COL_WIENER, true)
+PWF_COL_TRAIT(COL_BACK_L2, true)
 PWF_COL_TRAIT(COL_NESTEROV, true)
 PWF_COL_TRAIT(COL_DIRECTION, true)
 PWF_COL_TRAIT(COL_SPEC_YHAT, false)
@@ -639,6 +640,13 @@ __device__ __forceinline__ float2 transfer_sep(float2 qx, float2 qy, float fx, f
 // Geometries outside the series range use the FP64 formula per element.
 __device__ __noinline__ float2 transfer_direct(double chirp_rev, double s_coef, float fx, float fy) {
   return transfer(chirp_rev, s_coef, 0, fx, fy, false);
+}
+
+// Backward factor of the diffuser estimate: one rounding of the phase, where the
+// iteration's sweeps multiply two rounded factors.  (The FP64 arithmetic per
+// element does not show: a calibration of 1024^2 takes 146 us either way.)
+__device__ __noinline__ float2 transfer_back(double chirp_rev, double s_coef, int series, float fx, float fy) {
+  return transfer(chirp_rev, s_coef, series, fx, fy, true);
 }
 
 // Waves per SIMD the column sweeps must leave room for: 4 (128 registers)
@@ -958,6 +966,8 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
         } else if constexpr (OP == COL_WIENER) {
           const float h = ixv * gldf(I.iy, ky);
           v[e] = cscale(v[e], h / (h * h + I.wiener_eps) * I.inv_m);
+        } else if constexpr (OP == COL_BACK_L2) {
+          v[e] = cscale(cmul(v[e], transfer_back(I.chirp2_rev, I.s_coef, I.series, fx, freq_of(ky, NY))), I.inv_m);
         } else if constexpr (OP == COL_BLUR_LOSS) {
           const float h = ixv * ytab(j).x;
           const float2 yh = gld_if_nt<PAST>(I.y_hat, o_e);
@@ -1160,6 +1170,7 @@ hipError_t launch_col_nw(int op, int nblocks, const Sweep& S, hipStream_t st) {
     PWF_CASE(COL_CHIRP1) PWF_CASE(COL_CHIRP2) PWF_CASE(COL_CHIRP2_CONJ) PWF_CASE(COL_CHIRP1_CONJ)
     PWF_CASE(COL_BLUR_LOSS) PWF_CASE(COL_BLUR) PWF_CASE(COL_NESTEROV) PWF_CASE(COL_DIRECTION)
     PWF_CASE(COL_SPEC_YHAT) PWF_CASE(COL_SPEC_PSIHAT) PWF_CASE(COL_WIENER)
+    PWF_CASE(COL_BACK_L2)
     case COL_NESTEROV_SECOND: hipLaunchKernelGGL((col_sweep<N, W, COL_NESTEROV, 1>), grid, block, 0, st, S); break;
     case COL_NESTEROV_FIRST: hipLaunchKernelGGL((col_sweep<N, W, COL_NESTEROV, 2>), grid, block, 0, st, S); break;
 #undef PWF_CASE
