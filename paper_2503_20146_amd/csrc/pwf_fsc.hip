@@ -82,7 +82,8 @@ fsc_rows_kernel(const float2* __restrict__ g1, const float2* __restrict__ g2, in
   }
   __syncthreads();
   // split: with C = F{row0 + i row1}, 2 F{row0} = C(k) + conj C(-k) and
-  // 2 F{row1} = (C(k) - conj C(-k)) / i (the common factor leaves the correlation unchanged)
+  // 2 F{row1} = (C(k) - conj C(-k)) / i (the common factor leaves the correlation unchanged; a sum of two
+  // FP32 numbers is rounded once, as an FP64 one would be when it is stored)
   const int pl = (int)threadIdx.x / (2 * T), u = (int)threadIdx.x % (2 * T);
   const LdsView la{lds + 2 * pl * lds_len(N), 1}, lb{lds + (2 * pl + 1) * lds_len(N), 1};
   float4* __restrict__ out = dst + 2 * ((size_t)b * (RW / 2) + pl) * (N / 2);
@@ -170,8 +171,7 @@ fsc_cols_kernel(float2* __restrict__ a, size_t nx, size_t plane_stride, int tile
 // The workgroup then adds its waves' histograms in wave order and writes one
 // row of partials.  Four waves per workgroup up to n = 1024 and two at 2048
 // keep the histograms at 49 KB of LDS.
-__device__ __forceinline__ void shell_add(double (&s)[3], float2 a, float2 b, double w) {
-  const double ax = a.x, ay = a.y, bx = b.x, by = b.y;
+__device__ __forceinline__ void shell_add(double (&s)[3], double ax, double ay, double bx, double by, double w) {
   s[0] += w * (ax * bx + ay * by);
   s[1] += w * (ax * ax + ay * ay);
   s[2] += w * (bx * bx + by * by);
@@ -189,6 +189,12 @@ __global__ void __launch_bounds__(kFscThreads) fsc_shell_kernel(const float4* __
   for (int i = threadIdx.x; i < waves * 3 * nsh; i += blockDim.x) sh[i] = 0.0;
   __syncthreads();
   double* h = sh + wave * 3 * nsh;
+  // (each sum converts its operands itself: held for all four sums they took 18 more registers and, at
+  // 512^3, a wave per SIMD: 1.69 -> 1.77 ms)
+  auto sum = [](float a, float b) {
+    asm volatile("" : "+v"(a), "+v"(b));
+    return (double)a + (double)b;
+  };
   auto put = [&](int k, double x0, double x1, double x2) {
     if (k < nsh) {
       h[k] += x0;
@@ -231,18 +237,17 @@ __global__ void __launch_bounds__(kFscThreads) fsc_shell_kernel(const float4* __
         double ny[3] = {0.0, 0.0, 0.0};   // kx = n/2
 #pragma unroll
         for (int i = 0; i < NR / 2; ++i) {
+          // P = X0 + i Xn with X0, Xn Hermitian: 2 X0 = P(k) + conj P(-k), 2 Xn = (P(k) - conj P(-k)) / i,
+          // separated in FP64 (the weight takes the factor of 2)
           const float4 u = p[i][j], m = p[NR - 1 - i][j];
-          // P = X0 + i Xn with X0, Xn Hermitian: X0 = (P(k) + conj P(-k)) / 2, Xn = (P(k) - conj P(-k)) / 2i
-          shell_add(v, make_float2(0.5f * (u.x + m.x), 0.5f * (u.y - m.y)),
-                    make_float2(0.5f * (u.z + m.z), 0.5f * (u.w - m.w)), 2.0 * wr);
-          shell_add(ny, make_float2(0.5f * (u.y + m.y), 0.5f * (m.x - u.x)),
-                    make_float2(0.5f * (u.w + m.w), 0.5f * (m.z - u.z)), 2.0 * wr);
+          shell_add(v, sum(u.x, m.x), sum(u.y, -m.y), sum(u.z, m.z), sum(u.w, -m.w), 0.5 * wr);
+          shell_add(ny, sum(u.y, m.y), sum(m.x, -u.x), sum(u.w, m.w), sum(m.z, -u.z), 0.5 * wr);
         }
         put((int)rintf(sqrtf((float)H * (float)H + r2)), ny[0], ny[1], ny[2]);   // (this lane alone)
       } else {
 #pragma unroll
         for (int i = 0; i < NR; ++i)
-          shell_add(v, make_float2(p[i][j].x, p[i][j].y), make_float2(p[i][j].z, p[i][j].w), 2.0 * wr);
+          shell_add(v, p[i][j].x, p[i][j].y, p[i][j].z, p[i][j].w, 2.0 * wr);
       }
       if (sk[j] == nsh) v[0] = v[1] = v[2] = 0.0;
       if (j == 0) {
