@@ -577,17 +577,12 @@ struct Launcher {
   hipStream_t st;
   double corr_tol = 0.0;
   bool merged = false;   // batch_merged(B): one launch per sweep over the classes
-  bool latency = false;  // the latency plans, where nothing is set (forward calls)
   int width_of(const Class& c, int op) const {
     if (op == pwf::COL_NESTEROV_FIRST || op == pwf::COL_NESTEROV_SECOND) op = pwf::COL_NESTEROV;
-    const bool set = g_col_width[size_index(c.ny)][op] != 0;
-    return latency && !set && pwf::latency_shape(c.nx, c.ny, c.count) ? pwf::kLatencyWidth
-                                                                      : class_col_width(c.nx, c.ny, c.count, op);
+    return class_col_width(c.nx, c.ny, c.count, op);
   }
   int plan_of(const Class& c, int op) const {
-    if (op == pwf::ROW_PSI_UPDATE_CORR) op = pwf::ROW_PSI_UPDATE;
-    const bool set = pwf::row_plan_tunable(op) && g_row_plan[size_index(c.nx)][op] >= 0;
-    return latency && !set && pwf::latency_shape(c.nx, c.ny, c.count) ? 2 : row_plan(c.nx, op);
+    return row_plan(c.nx, op == pwf::ROW_PSI_UPDATE_CORR ? (int)pwf::ROW_PSI_UPDATE : op);
   }
   Inst* dev_desc() const { return (Inst*)(ws + L.desc); }
   int32_t* status() const { return (int32_t*)(ws + L.status); }
@@ -635,7 +630,6 @@ struct Launcher {
     for (const Class& c : B.classes) {
       Sweep S = sweep(c, iter);
       const int width = width_of(c, op);
-      if (c.ny <= 256 && width == pwf::kLatencyWidth) S.tw_col = ctx.twa2[size_index(c.ny)];   // its plan is the rows' third
       set_blocks(S, col_blocks(c.nx, c.ny, op, width));
       PWF_HIP(pwf::launch_col(c.ny, width, op, S.blocks_per_inst * c.count, S, st));
     }
@@ -840,8 +834,7 @@ pwf_status forward_impl(const pwf_problem* problems, int32_t n, const void* cons
     }
   }
   PWF_TRY(setup(*ctx, ws, L, desc.data(), n, false, st));
-  Launcher K{*ctx, ws, L, B, st};
-  K.latency = true;
+  const Launcher K{*ctx, ws, L, B, st};
   PWF_TRY(K.row(pwf::ROW_START));
   PWF_TRY(K.col(pwf::COL_CHIRP1));
   PWF_TRY(K.row(pwf::ROW_MUL_T));

@@ -204,10 +204,7 @@ template <> struct RowCfgAlt<1024> { using Plan = FftPlan<1024, 16, 16, 4>; stat
 template <> struct RowCfgAlt<2048> { using Plan = FftPlan<2048, 16, 16, 8>; static constexpr int T = 128, RW = 2; };
 // A third plan on the large sides: the alternative plan's radices in the other
 // order (small radix first), searched by the autotuner.
-// On the small sides it is the plan of latency-bound forward calls (latency_shape).
 template <int N> struct RowCfgAlt2 : RowCfg<N> {};
-template <> struct RowCfgAlt2<128>  { using Plan = FftPlan<128, 4, 4, 4, 2>;  static constexpr int T = 32,  RW = 8; };
-template <> struct RowCfgAlt2<256>  { using Plan = FftPlan<256, 4, 4, 4, 4>;  static constexpr int T = 64,  RW = 4; };
 template <> struct RowCfgAlt2<1024> { using Plan = FftPlan<1024, 4, 16, 16>; static constexpr int T = 64,  RW = 4; };
 template <> struct RowCfgAlt2<2048> { using Plan = FftPlan<2048, 8, 16, 16>; static constexpr int T = 128, RW = 2; };
 template <int N> constexpr int row_plan_count() { return (N == 1024 || N == 2048) ? 3 : 2; }
@@ -227,30 +224,6 @@ template <> struct ColCfg<256>  { using Plan = FftPlan<256, 16, 16>;     static 
 template <> struct ColCfg<512>  { using Plan = FftPlan<512, 16, 8, 4>;   static constexpr int T = 32,  WA = 16, WB = 8; };
 template <> struct ColCfg<1024> { using Plan = FftPlan<1024, 16, 16, 4>; static constexpr int T = 64,  WA = 8,  WB = 16; };
 template <> struct ColCfg<2048> { using Plan = FftPlan<2048, 16, 16, 8>; static constexpr int T = 128, WA = 4,  WB = 8; };
-
-// Column configuration by tile width: 8-column tiles of 128- and 256-point
-// columns are those of latency-bound forward calls, with the row plans' four
-// elements per lane.
-constexpr int kLatencyWidth = 8;
-template <int N, int W> struct ColPlanSel : ColCfg<N> {};
-template <> struct ColPlanSel<128, kLatencyWidth> { using Plan = FftPlan<128, 4, 4, 4, 2>; static constexpr int T = 32; };
-template <> struct ColPlanSel<256, kLatencyWidth> { using Plan = FftPlan<256, 4, 4, 4, 4>; static constexpr int T = 64; };
-
-// Forward calls on batches of small grids that do not fill the chip: a wave's
-// own chain of arithmetic and LDS exchanges is then the time of a sweep, not the
-// memory.  At 16 elements per lane a 128^2 field is 16 waves of ~1500 operations
-// each; four elements per lane make it 64 waves of a third of that, for two more
-// LDS exchanges: 50.5 -> 42.7 us for pwf_forward of one 256^2 field; 64 fields of
-// 128^2 still gained (109 -> 96 us for twelve sweeps), 256 of them, bound by
-// memory, ran 2% slower.  The forward's result has the error of the built-in
-// plans (1.5e-7 of its norm).  The solves, gradients and steps stay on the
-// built-in plans, although one field of 128^2 ran its iterations 1.4 times as
-// fast: their results amplify the order of rounding, and those of a user's small
-// reconstructions would no longer be the same bits.
-constexpr int kLatencyPixels = 1 << 20;
-constexpr bool latency_shape(int nx, int ny, int count) {
-  return nx <= 256 && ny <= 256 && (long long)nx * ny * count <= kLatencyPixels;
-}
 
 // Radix-2 split of the column transforms of the sweeps on sides of 512 and
 // more.  A 2048-point column needs 16 KB of LDS, so a tile of 8 columns

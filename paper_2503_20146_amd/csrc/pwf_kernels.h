@@ -37,10 +37,6 @@ constexpr bool row_plan_tunable(int op) {
   return op == ROW_PSI_UPDATE || op == ROW_MUL_T || op == ROW_INTENSITY || op == ROW_BACKBLUR ||
          op == ROW_MUL_CONJ_T || op == ROW_GRAD;
 }
-// Row sweeps of the forward model (those that the latency plans are built for).
-constexpr bool row_op_forward(int op) {
-  return op == ROW_START || op == ROW_MUL_T || op == ROW_INTENSITY || op == ROW_FORWARD_OUT;
-}
 template <int N> constexpr bool row_alt_default(int op) {
   return op == ROW_PSI_UPDATE || (N == 1024 && row_plan_tunable(op)) ||
          (N == 2048 && (op == ROW_GRAD || op == ROW_INTENSITY));

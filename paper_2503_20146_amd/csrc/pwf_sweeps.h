@@ -666,7 +666,7 @@ template <int NY, int W, int OP> constexpr int col_min_waves() {
 template <int NY, int W>
 struct ColLds {
   static constexpr int NF = col_fft_len<NY>();
-  using TS = TwSel<typename ColPlanSel<NF, W>::Plan, 1, true>;
+  using TS = TwSel<typename ColCfg<NF>::Plan, 1, true>;
   static constexpr int kExchange = W * lds_len(NF);
   static constexpr int kTwiddles = TS::kLds;
   static constexpr int kYTable = NF / 2 + 1;  // chirp sweeps: staged y factors
@@ -690,7 +690,7 @@ template <int NY, int W, int OP, int ZEROS = 0>
 __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, float2* twl, float2* qyl) {
   constexpr bool SPLIT = col_split<NY>();
   constexpr int NF = col_fft_len<NY>();
-  using C = ColPlanSel<NF, W>;
+  using C = ColCfg<NF>;
   using Plan = typename C::Plan;
   constexpr int T = C::T, E = NF / T;
   constexpr int R1 = Plan::radix[0], RL = Plan::radix[Plan::NPASS - 1];
@@ -1008,10 +1008,8 @@ __device__ __forceinline__ void col_body(const Sweep& S, int b, float2* lds, flo
   }
 }
 
-template <int NY, int W> constexpr int col_threads() { return ColPlanSel<col_fft_len<NY>(), W>::T * W; }
-
 template <int NY, int W, int OP, int ZEROS = 0>
-__global__ void __launch_bounds__((col_threads<NY, W>()), (col_min_waves<NY, W, OP>())) col_sweep(Sweep S) {
+__global__ void __launch_bounds__(ColSweepCfg<NY>::T * W, (col_min_waves<NY, W, OP>())) col_sweep(Sweep S) {
   __shared__ float2 lds[ColLds<NY, W>::kExchange];
   __shared__ float2 twl[ColLds<NY, W>::kTwiddles];
   __shared__ float2 qyl[col_op_ystage(OP) ? ColLds<NY, W>::kYTable : 1];
@@ -1106,13 +1104,12 @@ hipError_t launch_row_one(int nblocks, const Sweep& S, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Row sweep `op` with radix plan `plan` (tunable sweeps only; the others run
-// with their default plan, and those of the forward model on the small sides
-// also with the latency plan).
+// Row sweep `op` with radix plan `plan` (tunable sweeps only; the others
+// always run with their default plan).
 template <int N, int OP, bool PAIR>
 hipError_t launch_row_plan(int plan, int nblocks, const Sweep& S, hipStream_t st) {
   if (plan == 1) return launch_row_one<N, OP, 1, PAIR>(nblocks, S, st);
-  if constexpr (row_plan_count<N>() > 2 || (N <= 256 && !PAIR && row_op_forward(OP))) {
+  if constexpr (row_plan_count<N>() > 2) {
     if (plan == 2) return launch_row_one<N, OP, 2, PAIR>(nblocks, S, st);
   }
   if (plan == 0) return launch_row_one<N, OP, 0, PAIR>(nblocks, S, st);
@@ -1123,12 +1120,7 @@ template <int N, bool PAIR>
 hipError_t launch_row_np(int op, int plan, int nblocks, const Sweep& S, hipStream_t st) {
   switch (op) {
 #define PWF_TUNABLE(o) case o: return launch_row_plan<N, o, PAIR>(plan, nblocks, S, st);
-#define PWF_FIXED(o)                                                                                    \
-  case o:                                                                                               \
-    if constexpr (N <= 256 && !PAIR && row_op_forward(o)) {                                             \
-      if (plan == 2) return launch_row_one<N, o, 2, PAIR>(nblocks, S, st);                              \
-    }                                                                                                   \
-    return launch_row_one<N, o, row_alt_default<N>(o) ? 1 : 0, PAIR>(nblocks, S, st);
+#define PWF_FIXED(o) case o: return launch_row_one<N, o, row_alt_default<N>(o) ? 1 : 0, PAIR>(nblocks, S, st);
     PWF_TUNABLE(ROW_PSI_UPDATE) PWF_TUNABLE(ROW_PSI_UPDATE_CORR) PWF_TUNABLE(ROW_MUL_T) PWF_TUNABLE(ROW_MUL_CONJ_T) PWF_TUNABLE(ROW_INTENSITY)
     PWF_TUNABLE(ROW_BACKBLUR) PWF_TUNABLE(ROW_GRAD)
     PWF_FIXED(ROW_START) PWF_FIXED(ROW_FORWARD_OUT) PWF_FIXED(ROW_REAL_FFT) PWF_FIXED(ROW_CPLX_FFT)
@@ -1147,23 +1139,9 @@ hipError_t launch_row_n(int op, int plan, int nblocks, const Sweep& S, hipStream
                          : launch_row_np<N, false>(op, plan, nblocks, S, st);
 }
 
-// Column sweep `op` of the forward model on the latency plan (side <= 256).
-template <int N>
-hipError_t launch_col_latency(int op, int nblocks, const Sweep& S, hipStream_t st) {
-  constexpr int W = kLatencyWidth;
-  const dim3 grid(nblocks), block(col_threads<N, W>());
-  switch (op) {
-#define PWF_CASE(o) case o: hipLaunchKernelGGL((col_sweep<N, W, o>), grid, block, 0, st, S); break;
-    PWF_CASE(COL_CHIRP1) PWF_CASE(COL_CHIRP2) PWF_CASE(COL_BLUR)
-#undef PWF_CASE
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 template <int N, int W>
 hipError_t launch_col_nw(int op, int nblocks, const Sweep& S, hipStream_t st) {
-  using C = ColPlanSel<col_fft_len<N>(), W>;
+  using C = ColSweepCfg<N>;
   const dim3 grid(nblocks), block(C::T * W);
   switch (op) {
 #define PWF_CASE(o) case o: hipLaunchKernelGGL((col_sweep<N, W, o>), grid, block, 0, st, S); break;
@@ -1184,9 +1162,6 @@ hipError_t launch_col_n(int width, int op, int nblocks, const Sweep& S, hipStrea
   using C = ColSweepCfg<N>;
   if (width == C::WA) return launch_col_nw<N, C::WA>(op, nblocks, S, st);
   if (width == C::WB) return launch_col_nw<N, C::WB>(op, nblocks, S, st);
-  if constexpr (N <= 256) {
-    if (width == kLatencyWidth) return launch_col_latency<N>(op, nblocks, S, st);
-  }
   return hipErrorInvalidValue;
 }
 
