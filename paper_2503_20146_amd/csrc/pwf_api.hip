@@ -1134,7 +1134,9 @@ pwf_status solve_start(const Launcher& K) {
 pwf_status solve_iterations(const Launcher& K, const pwf_problem* probs, int n, int iters, const JointCfg& jc) {
   const int s0 = K.corr_tol > 0.0 ? pwf::ROW_PSI_UPDATE_CORR : pwf::ROW_PSI_UPDATE;
   if (iters == 0)   // psi = 0, by the final pass
-    PWF_HIP(pwf::launch_fill_zero(K.ws + K.L.W[K.B.order[0]], K.L.psi_hat[K.B.order[0]] - K.L.W[K.B.order[0]], K.st));
+    for (const Class& c : K.B.classes)   // (the launcher's own: other classes may run on other streams)
+      PWF_HIP(pwf::launch_fill_zero(K.ws + K.L.W[K.B.order[c.first]],
+                                    field_bytes(probs[K.B.order[c.first]]) * c.count, K.st));
   auto row = [&](int op, int k) { return K.merged ? K.row_merged(op, k) : K.row(op, k); };
   auto col = [&](int op, int k) { return K.merged ? K.col_merged(op, k) : K.col(op, k); };
   for (int k = 0; k < iters; ++k) {
