@@ -235,7 +235,11 @@ pwf_status pwf_step(const pwf_problem* problems, int32_t n, pwf_state* states, d
  *               and loss_hist entries past its stop are left untouched.  The
  *               call then synchronises on `stream` to fill iters_done.
  *   iters_done  host int32 [n] or NULL: iterations done per instance
- * With graph mode on (the default) the whole loop is one hipGraph launch. */
+ * With graph mode on (the default) the whole loop is one hipGraph launch, or one
+ * per grid shape of the batch on streams side by side.  The captured graphs of
+ * the last 16 solves per device are kept; a call that finds them all in flight
+ * launches its sweeps directly instead (it never waits for a graph).  So does a
+ * call on a stream under capture: its sweeps become part of the caller's graph. */
 pwf_status pwf_solve(const pwf_problem* problems, int32_t n, const float* const* y, void* const* psi_out,
                      int32_t iters, double corr_tol, double* loss_hist, int32_t* iters_done, void* workspace,
                      size_t workspace_bytes, void* stream);

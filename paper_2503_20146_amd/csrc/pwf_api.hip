@@ -71,18 +71,18 @@ struct Context {
   static constexpr int kForks = 3;
   hipStream_t fork[kForks] = {};
   hipEvent_t fork_ev[kForks + 1] = {};
-  // Captured solve loops.  Each graph is one chain of launches: the size classes
-  // of an uneven batch have a graph each, launched side by side on streams of
-  // their own.  The least recently used one makes room for a new one, once its
-  // last launch has ended (`done`).
-  struct CachedGraph {
-    hipGraphExec_t exec = nullptr;
+  // Captured solves: a graph of each chain of launches (one, or one per size class
+  // of an uneven batch, launched side by side).  At most kSolves solves, whatever
+  // their class counts; the least recently used one makes room for a new one, if
+  // its last call has ended (`done`).
+  struct CachedSolve {
+    std::vector<hipGraphExec_t> graphs;   // null: not captured yet
     hipEvent_t done = nullptr;
     uint64_t used = 0;
   };
-  static constexpr size_t kGraphs = 16;
-  std::map<GraphKey, CachedGraph> graphs;
-  uint64_t graph_uses = 0;
+  static constexpr size_t kSolves = 16;
+  std::map<GraphKey, CachedSolve> solves;
+  uint64_t solve_uses = 0;
   // pinned staging for descriptor uploads (ring of slots)
   static constexpr int kSlots = 4;
   void* stage[kSlots] = {};
@@ -1159,22 +1159,54 @@ pwf_status solve_iterations(const Launcher& K, const pwf_problem* probs, int n, 
   return K.row(pwf::ROW_IFFT_OUT, iters);
 }
 
-// Launch the graph of `key` on `s`, captured by `enqueue(stream)` if it is not cached.
-template <class F>
-pwf_status launch_graph(Context& c, const GraphKey& key, hipStream_t s, F enqueue) {
-  auto it = c.graphs.find(key);
-  if (it == c.graphs.end()) {
-    while (c.graphs.size() >= Context::kGraphs) {
-      auto old = c.graphs.begin();
-      for (auto g = c.graphs.begin(); g != c.graphs.end(); ++g)
-        if (g->second.used < old->second.used) old = g;
-      (void)hipEventSynchronize(old->second.done);   // a launch in flight keeps using the graph
-      (void)hipGraphExecDestroy(old->second.exec);
-      (void)hipEventDestroy(old->second.done);
-      c.graphs.erase(old);
+// Whether `st` is being captured by the caller.
+bool stream_captured(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cs != hipStreamCaptureStatusNone;
+}
+
+void drop_solve(Context::CachedSolve& e) {
+  for (hipGraphExec_t g : e.graphs)
+    if (g) (void)hipGraphExecDestroy(g);
+  if (e.done) (void)hipEventDestroy(e.done);
+}
+
+// The cached solve of `key`, made (with `chains` graphs still to capture) if it is
+// not there.  Null where the cache is full of solves and the least recently used
+// one is still in flight: the call then launches without graphs, since it must
+// neither wait for that solve on the host nor drop what the device still runs.
+Context::CachedSolve* cached_solve(Context& c, const GraphKey& key, size_t chains) {
+  auto it = c.solves.find(key);
+  if (it == c.solves.end()) {
+    if (c.solves.size() >= Context::kSolves) {
+      auto old = c.solves.begin();
+      for (auto e = c.solves.begin(); e != c.solves.end(); ++e)
+        if (e->second.used < old->second.used) old = e;
+      if (hipEventQuery(old->second.done) != hipSuccess) {
+        (void)hipGetLastError();   // (not ready)
+        return nullptr;
+      }
+      drop_solve(old->second);
+      c.solves.erase(old);
     }
+    Context::CachedSolve e;
+    if (hipEventCreateWithFlags(&e.done, hipEventDisableTiming) != hipSuccess) return nullptr;
+    e.graphs.resize(chains);
+    it = c.solves.emplace(key, std::move(e)).first;
+  }
+  it->second.used = ++c.solve_uses;
+  return &it->second;
+}
+
+// Launch `exec` on `s`, captured by `enqueue(stream)` if it has not been yet.
+template <class F>
+pwf_status launch_graph(Context& c, hipGraphExec_t& exec, hipStream_t s, F enqueue) {
+  if (!exec) {
     hipGraph_t graph = nullptr;
-    Context::CachedGraph g;
     PWF_HIP(hipStreamBeginCapture(c.side, hipStreamCaptureModeThreadLocal));
     const pwf_status cs = enqueue(c.side);
     const hipError_t ee = hipStreamEndCapture(c.side, &graph);
@@ -1182,18 +1214,12 @@ pwf_status launch_graph(Context& c, const GraphKey& key, hipStream_t s, F enqueu
       if (graph) (void)hipGraphDestroy(graph);
       return cs != PWF_OK ? cs : PWF_ERR_HIP;
     }
-    const hipError_t ie = hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0);
+    const hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
+    if (ie != hipSuccess) exec = nullptr;
     PWF_HIP(ie);
-    if (hipEventCreateWithFlags(&g.done, hipEventDisableTiming) != hipSuccess) {
-      (void)hipGraphExecDestroy(g.exec);
-      return PWF_ERR_HIP;
-    }
-    it = c.graphs.emplace(key, g).first;
   }
-  it->second.used = ++c.graph_uses;
-  PWF_HIP(hipGraphLaunch(it->second.exec, s));
-  PWF_HIP(hipEventRecord(it->second.done, s));
+  PWF_HIP(hipGraphLaunch(exec, s));
   return PWF_OK;
 }
 
@@ -1292,20 +1318,30 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
   }
 
   const int nc = (int)B.classes.size();
-  if (nc <= 1 || jc.on || merged) {
-    auto all = [&](hipStream_t s) -> pwf_status {
-      PWF_TRY(start(s));
-      return solve_iterations(launcher(B, s), problems, n, iters, jc);
-    };
-    if (!g_graph_mode) {
+  const bool one_chain = nc <= 1 || jc.on || merged;
+  auto all = [&](hipStream_t s) -> pwf_status {
+    PWF_TRY(start(s));
+    return solve_iterations(launcher(B, s), problems, n, iters, jc);
+  };
+  // Under the caller's own capture every launch goes into that graph, on the
+  // caller's stream alone: a stream of the library that joined the capture
+  // would stay in it after the call, where other calls use it.
+  if (stream_captured(st)) {
+    PWF_TRY(all(st));
+    return report();
+  }
+  Context::CachedSolve* cached = g_graph_mode ? cached_solve(*ctx, key, one_chain ? 1 : nc) : nullptr;
+  if (one_chain) {
+    if (!cached) {
       PWF_TRY(all(st));
       return report();
     }
     PWF_HIP(hipEventRecord(ctx->ev_in, st));
     PWF_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_in, 0));
-    PWF_TRY(launch_graph(*ctx, key, ctx->side, all));
+    PWF_TRY(launch_graph(*ctx, cached->graphs[0], ctx->side, all));
     PWF_HIP(hipEventRecord(ctx->ev_out, ctx->side));
     PWF_HIP(hipStreamWaitEvent(st, ctx->ev_out, 0));
+    PWF_HIP(hipEventRecord(cached->done, st));
     return report();
   }
 
@@ -1314,8 +1350,8 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
   // round-robin), forked from and joined back into st with events, so that a
   // small class's short launches overlap the large ones instead of alternating
   // with them.  Each class is a graph of its own: one graph with the classes as
-  // branches took longer, and the runtime has ended in a fault where such graphs
-  // were made and dropped in turn.
+  // branches took longer (24 x 512^2 + 32 x 1024^2 + 8 x 2048^2, 10 iterations:
+  // 39.5 -> 38.8 ms).
   PWF_TRY(start(st));
   PWF_HIP(hipEventRecord(ctx->fork_ev[0], st));
   const int ns = std::min(nc, Context::kForks + 1);
@@ -1328,19 +1364,14 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
     one.order = B.order;
     one.classes = {B.classes[c]};
     auto iterations = [&](hipStream_t s) { return solve_iterations(launcher(one, s), problems, n, iters, jc); };
-    if (g_graph_mode) {
-      GraphKey ck = key;
-      ck.dims.push_back(c);
-      rc = launch_graph(*ctx, ck, stream_of(c), iterations);
-    } else {
-      rc = iterations(stream_of(c));
-    }
+    rc = cached ? launch_graph(*ctx, cached->graphs[c], stream_of(c), iterations) : iterations(stream_of(c));
   }
   for (int j = 0; j < ns; ++j) {   // (also after an error: what was launched still uses the workspace)
     hipEvent_t e = j == 0 ? ctx->ev_out : ctx->fork_ev[j];
     PWF_HIP(hipEventRecord(e, stream_of(j)));
     PWF_HIP(hipStreamWaitEvent(st, e, 0));
   }
+  if (cached) PWF_HIP(hipEventRecord(cached->done, st));
   PWF_TRY(rc);
   return report();
 }
@@ -2261,12 +2292,11 @@ void pwf_finalize(void) {
   std::lock_guard<std::mutex> lk(g_mu);
   for (Context& c : g_ctx) {
     if (!c.ready) continue;
-    for (auto& kv : c.graphs) {
+    for (auto& kv : c.solves) {
       (void)hipEventSynchronize(kv.second.done);
-      (void)hipGraphExecDestroy(kv.second.exec);
-      (void)hipEventDestroy(kv.second.done);
+      drop_solve(kv.second);
     }
-    c.graphs.clear();
+    c.solves.clear();
     for (float2*& t : c.tw) {
       if (t) (void)hipFree(t);
       t = nullptr;
