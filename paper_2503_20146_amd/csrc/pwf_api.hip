@@ -730,16 +730,28 @@ pwf_status launch_maxt2(const pwf_problem* probs, int n, const Batch& B, const s
   return PWF_OK;
 }
 
+// Whether `st` is being captured by the caller.
+bool stream_captured(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cs != hipStreamCaptureStatusNone;
+}
+
 // Set-up of a call: descriptors to the workspace, window tables, and, for calls
 // that compute a loss (`clear`), the status flag and the slots of max|t|^2 (in
 // front of the descriptors) cleared.  Up to kSetupLaunches x kSetupInsts
 // instances travel as kernel arguments (about 4 us a launch); a larger batch
 // through the pinned staging buffer, whose copy starts the first sweep some
-// 25 us later, small against the sweeps of such a batch.
+// 25 us later, small against the sweeps of such a batch.  (Not on a stream under
+// capture: the caller's graph would read the buffer again at every replay, when
+// it holds other calls' descriptors.)
 constexpr int kSetupLaunches = 4;
 constexpr int kSetupByArgs = kSetupLaunches * pwf::kSetupInsts;
 pwf_status setup(Context& c, char* ws, const Layout& L, const Inst* desc, int n, bool clear, hipStream_t st) {
-  if (n <= kSetupByArgs) {
+  if (n <= kSetupByArgs || stream_captured(st)) {
     pwf::SetupArgs A;
     A.words = (uint32_t*)(ws + L.status);
     A.clear = clear ? (int32_t)((L.desc - L.status) / 4) : 0;
@@ -1157,16 +1169,6 @@ pwf_status solve_iterations(const Launcher& K, const pwf_problem* probs, int n, 
     if (jc.on) PWF_TRY(joint_step(K, probs, n, jc));
   }
   return K.row(pwf::ROW_IFFT_OUT, iters);
-}
-
-// Whether `st` is being captured by the caller.
-bool stream_captured(hipStream_t st) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return cs != hipStreamCaptureStatusNone;
 }
 
 void drop_solve(Context::CachedSolve& e) {
@@ -2264,10 +2266,10 @@ pwf_status pwf_loss_grad_noalloc(const pwf_problem* problems, int32_t n, const v
   hipStream_t st = (hipStream_t)stream;
   char* ws = d->base + kScratchTableBytes;
   const Batch B = group(problems, n);
-  if (n <= kSetupByArgs) {   // as kernel arguments: nothing on the host outlives the call
-    Inst desc[kSetupByArgs];
-    loss_grad_descriptors(problems, n, B, psi, y, grad_out, loss_out, ws, L, desc);
-    PWF_TRY(setup(d->tables, ws, L, desc, n, true, st));
+  if (n <= kSetupByArgs || stream_captured(st)) {   // as kernel arguments: nothing on the host outlives the call
+    std::vector<Inst> desc(n);
+    loss_grad_descriptors(problems, n, B, psi, y, grad_out, loss_out, ws, L, desc.data());
+    PWF_TRY(setup(d->tables, ws, L, desc.data(), n, true, st));
     return loss_grad_sequence(Launcher{d->tables, ws, L, B, st});
   }
   // the previous call's copy must have read host_desc before it is rewritten

@@ -5,8 +5,8 @@ caller's own graph.
   than it keeps; more grid shapes in one batch than solves; batches of several shapes in turn) return
   before that kernel ends, with the results of the same calls made one at a time.
 * Solves of one and of several grid shapes captured into a caller's graph, as a first and as a later
-  call, with the library's own graphs on and off: every replay gives the bits of the eager call, with
-  other solves between the replays.
+  call, with the library's own graphs on and off, and a batch whose descriptors are staged outside a
+  capture: every replay gives the bits of the eager call, with other solves between the replays.
 """
 
 import dataclasses
@@ -96,3 +96,53 @@ def test_solve_in_a_callers_graph(shapes, warm, own_graphs):
             assert all(torch.equal(a, b) for a, b in zip(out, want)) and torch.equal(hist, want_hist)
     finally:
         set_graph_mode(True)
+
+
+def test_large_batch_in_a_callers_graph():
+    """More instances than a set-up launch or four carry: the graph holds its own descriptors."""
+    import torch
+    dev = device()
+    n = 45
+    batch, y = make_batch([(128, 128)] * n, 7, dev)
+    other, y2 = make_batch([(128, 256)] * n, 8, dev)
+    say(f"capture of a solve and a forward call of {n} instances")
+    other.solve(y2, 2)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out, hist = batch.solve(y, 2)
+        f = batch.forward(out)
+    want, want_hist = batch.solve(y, 2)
+    want_f = batch.forward(want)
+    for _ in range(6):
+        for o in out + f:
+            o.fill_(float("nan"))
+        for _ in range(5):   # (every slot of the staging ring is used by other calls)
+            other.forward(other.solve(y2, 1)[0])
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out + f, want + want_f)) and torch.equal(hist, want_hist)
+
+
+def test_large_noalloc_batch_in_a_callers_graph():
+    import torch
+    dev = device()
+    n = 45
+    batch, y = make_batch([(128, 128)] * n, 9, dev)
+    other, y2 = make_batch([(128, 128)] * n, 10, dev)
+    psi = [0.1 * torch.randn(128, 128, dtype=torch.complex64, device=dev) for _ in range(n)]
+    say(f"capture of the loss and gradient of {n} instances without a workspace")
+    want_loss, want = batch.loss_grad_noalloc(psi, y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        loss, grad = batch.loss_grad_noalloc(psi, y)
+    for _ in range(4):
+        for g in grad:
+            g.fill_(float("nan"))
+        other.loss_grad_noalloc(psi, y2)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(grad, want)) and torch.equal(loss, want_loss)
