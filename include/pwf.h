@@ -287,12 +287,15 @@ pwf_status pwf_bench_sweep(const pwf_problem* problems, int32_t n, int32_t sweep
  * those of pwf_forward / pwf_gradient) for grid side n.  Two widths are
  * compiled per side (128: 32/16, 256: 16/32, and over one half of the split
  * column transform of the larger sides (see the state layout above) 512:
- * 16/32, 1024: 16/8, 2048: 8/16); 0 restores the default.  PWF_ERR_SIZE / PWF_ERR_ARG for an
- * unsupported side, sweep or width.  Process-wide; applies to calls issued
- * afterwards. */
+ * 16/32, 1024: 16/8, 2048: 8/16); 0 restores the built-in choice: the first width
+ * of the pair, or, for S1, S3, S7, S9 and S11, the one that the size of the call's
+ * batch makes the faster (results have the same bits with either).  PWF_ERR_SIZE /
+ * PWF_ERR_ARG for an unsupported side, sweep or width.  Process-wide; applies to
+ * calls issued afterwards. */
 pwf_status pwf_set_column_tile(int32_t n, int32_t sweep, int32_t width);
 
-/* Current tile width of column sweep S`sweep` for side n (0 if unsupported). */
+/* Tile width set for column sweep S`sweep` of side n, or, while none is set, the
+ * default of the side (0 if unsupported). */
 int32_t pwf_column_tile(int32_t n, int32_t sweep);
 
 /* FFT plan of the row sweep S`sweep` of the iteration (sweep = 0, 2, 4, 6, 8
@@ -323,7 +326,9 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
  * marked "/merged" when pwf_set_merged_launch(1) makes the batch launch
  * merged: the tuner then picks among what the merged kernels hold) and the
  * grid side, holding
- * that side's column-tile widths (S1..S11) and row plans (S0..S10).  When
+ * that side's column-tile widths (S1..S11; 0: not set) and row plans (S0..S10;
+ * -1: not set; a grid that is not square times only rows of one side and columns
+ * of the other).  When
  * every side of the batch has an entry for this architecture and mix, the
  * stored choices are applied and nothing is timed (*tuned = 0, tuned may be
  * NULL); otherwise, or with force != 0, pwf_autotune runs (same arguments)

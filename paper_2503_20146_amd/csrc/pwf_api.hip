@@ -1594,6 +1594,8 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
 // One line per (architecture, class mix, grid side):
 //   <arch> <mix> <side> c <w S1> <w S3> <w S5> <w S7> <w S9> <w S11> r <p S0> <p S2> ... <p S10>
 // mix lists the batch's grid shapes and instance counts, e.g. 512x512*24+1024x1024*32.
+// Width 0 and plan -1: not set (a batch of 1024 x 512 times no columns of 1024), so
+// that a process that reads the line makes the same choices as the one that wrote it.
 namespace {
 
 // Architecture of the current device and the library version: a cached
@@ -1630,9 +1632,10 @@ std::vector<int> batch_sides(const Batch& B) {
 
 std::string tuning_line(const std::string& arch, const std::string& mix, int side) {
   std::string l = arch + ' ' + mix + ' ' + std::to_string(side) + " c";
-  for (int sw = 1; sw < 12; sw += 2) l += ' ' + std::to_string(col_width(side, col_op_of_sweep(sw)));
+  const int i = size_index(side);
+  for (int sw = 1; sw < 12; sw += 2) l += ' ' + std::to_string(g_col_width[i][col_op_of_sweep(sw)]);
   l += " r";
-  for (int sw = 0; sw < 12; sw += 2) l += ' ' + std::to_string(row_plan(side, row_op_of_sweep(sw)));
+  for (int sw = 0; sw < 12; sw += 2) l += ' ' + std::to_string(g_row_plan[i][row_op_of_sweep(sw)]);
   return l;
 }
 
@@ -1651,7 +1654,8 @@ int apply_tuning_line(const std::string& line, const std::string& arch, const st
   const int i = size_index(side);
   if (i < 0) return 0;
   for (int k = 0; k < 6; ++k) {
-    if (!pwf::col_width_supported(side, w[k]) || pl[k] < 0 || pl[k] >= pwf::row_plan_count_n(side)) return 0;
+    if (w[k] != 0 && !pwf::col_width_supported(side, w[k])) return 0;
+    if (pl[k] < -1 || pl[k] >= pwf::row_plan_count_n(side)) return 0;
   }
   for (int k = 0; k < 6; ++k) {
     g_col_width[i][col_op_of_sweep(2 * k + 1)] = w[k];
