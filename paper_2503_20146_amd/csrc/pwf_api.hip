@@ -159,15 +159,19 @@ int g_merge_mode = 0;
 // Tile width of a column sweep for a class of `count` instances: what was set (by
 // the caller or the autotuner), else by the size of the batch.
 // - 1024-point columns, up to 10 M pixels: 8 columns instead of 16, twice the
-//   workgroups, where a launch has few waves of them or its fields fit the caches
-//   (S1, S11 in us, 16 -> 8 columns: one field 9.3, 14.7 -> 8.3, 11.7; nine 33.6,
-//   67.5 -> 30.1, 64.0; sixteen 52, 108 -> 51, 140: half lines of fields from
-//   memory, read twice, cost more).  Not S5, though it would gain as much: its loss
-//   partials are one per tile, and the loss of an instance keeps its bits in
-//   every batch.
+//   workgroups, where a launch has few waves of them or its fields fit the caches;
+//   beyond, half lines of fields from memory, read twice, cost S11 more (S1 .. S9
+//   alone would gain for longer; one line for all of them).  S1 and S11 in us,
+//   16 -> 8 columns, at 1024 x 1024: 1 M pixels 9.6, 13.5 -> 8.5, 11.5; 4 M 15.9, 33 ->
+//   15.3, 28; 10 M 34, 71 -> 31, 62; 12 M 39, 82 -> 35, 100; 16 M 50, 103 -> 45, 140.
+//   The pixels decide, not the rows' length: S11 with 128, 256, 512 and 2048 columns
+//   at 10 M 71 .. 73 -> 62, at 12 M 82 .. 83 -> 100 .. 103.  Not S5, though it would
+//   gain as much: its loss partials are one per tile, and the loss of an instance
+//   keeps its bits in every batch.
 // - S11 of 2048-point columns, from 16 M pixels: 16 columns instead of 8, whole
-//   lines (4 fields 155 -> 132 us, 36 fields 1.42 -> 1.27 ms; 2 fields 56 -> 72: too
-//   few workgroups).
+//   lines (2048 x 2048: 8 M 51 -> 71 us, 12 M 106 -> 103, 16 M 155 -> 129, 48 M 446 ->
+//   408; 128 .. 1024 columns: 8 M 50 .. 53 -> 68 .. 70, 12 M 109 .. 113 -> 103 .. 106, 16 M
+//   144 .. 150 -> 125 .. 128).
 // (Merged launches hold one width per side, the default.)
 int class_col_width(int nx, int ny, int count, int op) {
   const long long pixels = (long long)nx * ny * count;

@@ -33,6 +33,11 @@ enum RowOp {
 // workload): the alternative plan (RowCfgAlt) for every tunable sweep at 1024,
 // for the update, intensity and gradient sweeps at 2048, for the update sweep
 // elsewhere.  Other row sweeps always use RowCfg.
+// (S2, S6 and S8 at 2048 would be faster on plan 2: 36 fields 656 -> 548, 611 -> 595
+// and 621 -> 540 us, 2.8% of the iteration; one field 28 -> 22, 25 -> 21, 27 -> 23.  It
+// rounds in another order, so every result at 2048 would have other bits; they stay
+// until its error against 64 bits has been measured over that range.  The autotuner
+// offers it.)
 constexpr bool row_plan_tunable(int op) {
   return op == ROW_PSI_UPDATE || op == ROW_MUL_T || op == ROW_INTENSITY || op == ROW_BACKBLUR ||
          op == ROW_MUL_CONJ_T || op == ROW_GRAD;
