@@ -840,7 +840,6 @@ pwf_status forward_impl(const pwf_problem* problems, int32_t n, const void* cons
     Inst& I = desc[s];
     I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
-    I.W = (float2*)(ws + L.W[i]);
     I.psi_src = (const float2*)psi[i];
     I.f_out = f_out[i];
     I.loss_partial = (double*)(ws + L.part[i]);
@@ -880,7 +879,6 @@ void loss_grad_descriptors(const pwf_problem* problems, int32_t n, const Batch& 
     Inst& I = desc[s];
     I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
-    I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
     I.x = (float2*)(ws + L.psi[i]);
     I.psi_src = (const float2*)psi[i];
@@ -953,7 +951,6 @@ pwf_status pwf_gradient(const pwf_problem* problems, int32_t n, const void* cons
     Inst& I = desc[s];
     I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
-    I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
     I.x = (float2*)(ws + L.psi[i]);
     I.psi_src = (const float2*)psi[i];
@@ -1037,7 +1034,6 @@ pwf_status pwf_state_init(const pwf_problem* problems, int32_t n, pwf_state* sta
     Inst& I = desc[s];
     I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
-    I.W = (float2*)(ws + L.W[i]);
     I.y = y[i];
     I.y_hat = (float2*)states[i].y_hat;
     I.psi_src = psi0 ? (const float2*)psi0[i] : nullptr;
@@ -1079,7 +1075,6 @@ pwf_status pwf_step(const pwf_problem* problems, int32_t n, pwf_state* states, d
     I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
     I.k0 = states[i].k;
-    I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
     I.x = (float2*)(ws + L.psi[i]);
     I.psi_src = (const float2*)states[i].psi;
@@ -1256,7 +1251,6 @@ pwf_status solve_impl(const pwf_problem* problems, int32_t n, const float* const
     Inst& I = desc[s];
     I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
-    I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
     I.x = (float2*)(ws + L.psi[i]);
     I.psi_hat = (float2*)(ws + L.psi_hat[i]);
@@ -1429,7 +1423,6 @@ pwf_status pwf_bench_sweep(const pwf_problem* problems, int32_t n, int32_t sweep
     Inst& I = desc[s];
     I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
-    I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
     I.x = (float2*)(ws + L.psi[i]);
     I.psi_hat = (float2*)(ws + L.psi_hat[i]);
@@ -1513,7 +1506,6 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
     Inst& I = desc[s];
     I = base_inst(problems[i]);
     attach_tables(I, ws, L, i);
-    I.W = (float2*)(ws + L.W[i]);
     I.v = (float2*)(ws + L.v[i]);
     I.x = (float2*)(ws + L.psi[i]);
     I.psi_hat = (float2*)(ws + L.psi_hat[i]);
@@ -1880,7 +1872,6 @@ pwf_status pwf_diffuser_from_reference(const pwf_problem* problem, const float* 
   char* ws = (char*)workspace;
   Inst I = base_inst(*problem);
   attach_tables(I, ws, L, 0);
-  I.W = (float2*)(ws + L.W[0]);
   I.y = ref;
   I.out = (float2*)t_out;
   I.wiener_eps = (float)eps;

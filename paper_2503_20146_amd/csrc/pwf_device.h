@@ -18,7 +18,6 @@ struct Inst {
   int32_t nx, ny;
   int32_t k0;           // iterations already done (momentum table offset)
   int32_t n_partials;   // number of loss partials (column tiles)
-  float2* W;            // work field between sweeps (the sweeps take it from Sweep::W)
   float2* v;            // detector field v, saved by the forward for the gradient
   float2* u1;           // joint diffuser mode: field incident on the diffuser (S2), then
                         // conj(u1) a2 (S8); null otherwise
