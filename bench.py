@@ -21,6 +21,7 @@ import hashlib
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -49,7 +50,6 @@ SWEEP_SOURCES = ["pwf_device.h", "pwf_fft.h", "pwf_sweeps.h", "pwf_sweeps_1024.h
 def kernel_source_hash() -> str:
     """Hash of the code of SWEEP_SOURCES with comments and whitespace removed (a change
     of comments leaves the kernels, and so the counters, as they were)."""
-    import re
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2503_20146_amd", "csrc")
     for f in SWEEP_SOURCES:
@@ -78,11 +78,11 @@ def measured_traffic(sweep: int, pixels: int, width: int = 0):
 
 
 COPY_BYTES = 1 << 30
-# kernel-name fragments of each fused sweep at 1024^2 (template op ids of row_sweep / col_sweep;
-# a row sweep's third template argument is its radix plan)
-SWEEP_KERNELS = ["row_sweep<1024, 0,", "col_sweep<1024, {w}, 0>", "row_sweep<1024, 2,", "col_sweep<1024, {w}, 1>",
-                 "row_sweep<1024, 4,", "col_sweep<1024, {w}, 4>", "row_sweep<1024, 5,", "col_sweep<1024, {w}, 2>",
-                 "row_sweep<1024, 3,", "col_sweep<1024, {w}, 3>", "row_sweep<1024, 6,", "col_sweep<1024, {w}, 6>"]
+# kernel-name patterns of each fused sweep at 1024^2 (template op ids of row_sweep / col_sweep;
+# a row sweep's third template argument is its radix plan, a column sweep's fourth the number
+# of zero states that a solve's first iterations do not read: 0 in the iterations counted here)
+SWEEP_KERNELS = [pattern for row, col in ((0, 0), (2, 1), (4, 4), (5, 2), (3, 3), (6, 6))
+                 for pattern in (rf"row_sweep<{{side}}, {row},", rf"col_sweep<{{side}}, {{w}}, {col}(, 0)?>")]
 
 
 TUNING_CACHE = os.path.join(ROOT, "paper_2503_20146_amd", "tuning_cache.txt")
@@ -154,9 +154,8 @@ def ingest_counters(fetch_csv: str, write_csv: str, projections: int, side: int 
     out = {"source_hash": kernel_source_hash(), "copy_bytes": COPY_BYTES, "side": side,
            "fetch_scale": f_scale, "write_scale": w_scale, "pixels_per_launch": pixels, "sweeps": {}}
     for s, frag in enumerate(SWEEP_KERNELS):
-        frag = frag.replace("<1024,", f"<{side},")
         for w in (4, 8, 16, 32):
-            names = [k for k in fetch if frag.format(w=w) in k]
+            names = [k for k in fetch if re.search(frag.format(side=side, w=w), k)]
             if not names:
                 continue
             name = names[0]
