@@ -321,7 +321,7 @@ pwf_status pwf_autotune(const pwf_problem* problems, int32_t n, int32_t reps, vo
 
 /* Autotuner with a persistent cache: a text file at cache_path (host path,
  * created when missing) keyed by the device's architecture with the library
- * version (e.g. "gfx950/v10301": entries timed on other kernels are not
+ * version (e.g. "gfx950/v10302": entries timed on other kernels are not
  * reused), the batch's class mix (its grid shapes and instance counts,
  * marked "/merged" when pwf_set_merged_launch(1) makes the batch launch
  * merged: the tuner then picks among what the merged kernels hold) and the

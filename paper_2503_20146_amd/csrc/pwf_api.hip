@@ -26,7 +26,7 @@ using pwf::Sweep;
 
 namespace {
 
-constexpr int kVersion = 10301;        // 1.3.1
+constexpr int kVersion = 10302;        // 1.3.2 (moved with every change of a timed kernel: it keys the tuning cache)
 constexpr int kBetaCap = 1 << 16;      // iterations covered by the momentum table
 constexpr size_t kAlign = 256;
 constexpr int kSizes[] = {128, 256, 512, 1024, 2048};

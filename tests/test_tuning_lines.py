@@ -58,3 +58,11 @@ def test_lines_with_every_sweep_set(tmp_path, line, want):
     assert out[0] == "0 0"
     # not applied: what was set before the call stays (S11 at 8 columns, plans built in)
     assert out[2] == want if want else out[2].startswith("[16, 16, 16, 16, 16, 8] ") and "[2, 1, 0" not in out[2]
+
+
+def test_shipped_entries_are_of_this_version():
+    from paper_2503_20146_amd import _lib
+    path = os.path.join(ROOT, "paper_2503_20146_amd", "tuning_cache.txt")
+    lines = [l.split() for l in open(path).read().splitlines()]
+    assert lines and {l[0] for l in lines} == {f"gfx950/v{_lib.load().pwf_version()}"}
+    assert all(len(l) == 17 and l[3] == "c" and l[10] == "r" for l in lines)
