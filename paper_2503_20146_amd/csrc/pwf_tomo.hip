@@ -116,7 +116,7 @@ hipError_t launch_fbp_filter(const float2* const* psi, int n_proj, int nx, int n
 // constant LDS offset), so S slices share them.  128 slices of 1024^2 from 180
 // angles: 10.5 operations per voxel, angle and slice with one slice and two
 // voxels a lane, 6.12 ms; 4.6 and 0.6 for staging with S = 8, 2 x 2 voxels,
-// 4.05 ms (6.0e12 interpolations a second, the ALU 95% busy).  Copying straight
+// 4.05 ms (6.0e12 interpolations a second, the vector ALU issuing in 93% of the cycles).  Copying straight
 // to LDS took 4.8 ms, the next chunk's loads held in registers 4.5 ms.
 constexpr int kFbpThreads = 256;
 constexpr int kFbpChunk = 4;     // angles per staged chunk
