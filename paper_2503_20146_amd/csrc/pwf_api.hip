@@ -172,11 +172,12 @@ int g_merge_mode = 0;
 //   lines (2048 x 2048: 8 M 51 -> 71 us, 12 M 106 -> 103, 16 M 155 -> 129, 48 M 446 ->
 //   408; 128 .. 1024 columns: 8 M 50 .. 53 -> 68 .. 70, 12 M 109 .. 113 -> 103 .. 106, 16 M
 //   144 .. 150 -> 125 .. 128).
-// (Merged launches hold one width per side, the default.)
+// (Merged launches hold one width per side, the default.  The back-propagation of
+// the diffuser estimate, S7 with other factors, goes with S7.)
 int class_col_width(int nx, int ny, int count, int op) {
   const long long pixels = (long long)nx * ny * count;
   const bool iteration = op == pwf::COL_CHIRP1 || op == pwf::COL_CHIRP2 || op == pwf::COL_CHIRP2_CONJ ||
-                         op == pwf::COL_CHIRP1_CONJ || op == pwf::COL_NESTEROV;
+                         op == pwf::COL_CHIRP1_CONJ || op == pwf::COL_NESTEROV || op == pwf::COL_BACK_L2;
   if (iteration && !g_merge_mode && g_col_width[size_index(ny)][op] == 0) {
     if (ny == 1024 && pixels <= 10 << 20) return 8;
     if (ny == 2048 && op == pwf::COL_NESTEROV && pixels >= 16 << 20) return 16;
